@@ -290,7 +290,8 @@ kvq_status kvq_decode_attn_noalloc(const kvq_cache* cache, const void* Q, int H_
  *   workspace  device scratch for the reconstructed blocks of each (b, h):
  *              every visible 32-token block is reconstructed once per call
  *              (192 D bytes each) and read back by all the chunk's query
- *              tiles.  kvq_prefill_workspace_bytes gives the size that
+ *              tiles; calls of few query rows reconstruct on the fly and keep
+ *              partial outputs there.  kvq_prefill_workspace_bytes gives the size that
  *              serves all B H_kv units in one pass; a smaller workspace
  *              (at least one unit's share, that size / (B H_kv)) makes the
  *              call process the units in groups that fit, with more

@@ -32,10 +32,11 @@ ROOT = os.path.dirname(HERE)
 # instructions, and AGPR accumulators cost a copy each way per block.
 _VGPR_MFMA = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
 # (source, object name, extra flags).  The decode split kernels are built
-# from one source, once per (head size, metadata width, key axis) family.
+# from one source, once per (head size, metadata width, key axis) family, the
+# prefill kernels once per head size.
 UNITS = [("kvq_api.cpp", "kvq_api", []), ("append.hip", "append", ["-ffp-contract=off"]),
-         ("attn.hip", "attn", _VGPR_MFMA), ("project.hip", "project", []), ("merge.hip", "merge", []),
-         ("prefill.hip", "prefill", [])]
+         ("attn.hip", "attn", _VGPR_MFMA), ("project.hip", "project", []), ("merge.hip", "merge", [])]
+UNITS += [("prefill.hip", f"prefill_{d}", [f"-DKVQ_PREFILL_D={d}"]) for d in (64, 128, 256)]
 UNITS += [("attn_part.hip", f"attn_{d}_{m}_{pc}",
            _VGPR_MFMA + [f"-DKVQ_PART_D={d}", f"-DKVQ_PART_M16={m}", f"-DKVQ_PART_PC={pc}"])
           for d in (64, 128, 256) for m in (0, 1) for pc in (0, 1)]

@@ -11,11 +11,21 @@
 // groups' scales and offsets in place of the lo half.  A rotating format's
 // keys and values are rotated back to the original basis (an fp32 FWHT per
 // token in LDS) before they are rounded, so queries and outputs need no
-// rotation.  dequant_kernel reconstructs every visible block of a unit once
-// into the caller's workspace and attn_kernel streams the images through an
-// LDS ring with global_load_lds_dwordx4.
+// rotation.  Two ways to the images, chosen by fused_splits:
 //
-// Each workgroup handles 256 query rows ((chunk token, head) pairs of a
+//   workspace  dequant_kernel reconstructs every visible block of a unit
+//              once into the caller's workspace and attn_kernel streams the
+//              images through an LDS ring with global_load_lds_dwordx4.
+//   fused      four waves of fused_kernel copy packed blocks into an LDS ring
+//              and reconstruct them there, one block ahead of the four waves
+//              that multiply: no image traffic, and the key range is split
+//              over workgroups (partials in the workspace, combined by
+//              merge_kernel) when the query tiles alone leave the chip idle.
+//              A 128-token chunk at the end of 8001 tokens (B = 4, 32 query
+//              heads on 8, D = 128, KIVI) had 64 workgroups: 398 -> 182 us;
+//              32 tokens at the end of 8192 (B = 1): 350 -> 34 to 49 us.
+//
+// Each workgroup handles 128 or 256 query rows ((chunk token, head) pairs of a
 // unit, token-major), each wave 32 QT of them, and per block:
 //   - scores S^T = K Q^T with v_mfma_f32_32x32x16_f16 (keys as rows, query
 //     rows as columns).  A bf16 query scaled by a power of two is exact in
@@ -50,29 +60,23 @@ namespace pre {
 
 constexpr int kDqThreads = 256;
 
-// Waves per attention workgroup: eight (one workgroup per CU, two waves per
-// SIMD), four at D = 64, where two workgroups share a CU (each SIMD holds
-// one wave of each, with independent per-block barriers).
+// Waves per workgroup of the workspace path: eight (one workgroup per CU, two
+// waves per SIMD), four at D = 64, where two workgroups share a CU (each SIMD
+// holds one wave of each, with independent per-block barriers).
 template <int D>
 constexpr int waves()
 {
     return D == 64 ? 4 : 8;
 }
 
-template <int D>
-constexpr int threads()
-{
-    return 64 * waves<D>();
-}
+constexpr int kRows = 256;  // query rows per workgroup
 
-// 32-row query tiles per wave: 256 rows per workgroup at every head size
+// 32-row query tiles per wave of the workspace path
 template <int D>
 constexpr int qtiles()
 {
     return D == 64 ? 2 : 1;
 }
-
-constexpr int kRows = 256;  // query rows per workgroup
 
 // One reconstructed 32-token block, 192 D bytes: K hi, K lo (64 D bytes
 // each), V (64 D bytes), all in fragment order.  K fragment s (channels 16 s
@@ -108,28 +112,17 @@ constexpr int stages()
 }
 
 // Query fragments per wave kept in LDS
-template <int D>
+template <int D, int KG>
 __host__ __device__ constexpr int query_lds_fragments()
 {
-    return D == 256 ? 2 : 0;
+    return D == 256 && KG > 0 ? 2 : 0;
 }
 
 // the ring, then the query fragments
 template <int D>
 constexpr size_t attn_lds_bytes()
 {
-    return (size_t)stages<D>() * image_bytes<D>() + (size_t)waves<D>() * query_lds_fragments<D>() * 1024;
-}
-
-__device__ __forceinline__ float dq(int mode, int bits, uint32_t c, float s, float z)
-{
-    return mode == KVQ_AFFINE ? (float)c * s + z : ((float)c - (float)(1 << (bits - 1))) * s;
-}
-
-// scale or offset i of a raw metadata range (fp32, or fp16 with meta16)
-__device__ __forceinline__ float meta(const uint8_t* sec, size_t i, bool m16)
-{
-    return m16 ? f16_bits_to_f32(((const uint16_t*)sec)[i]) : ((const float*)sec)[i];
+    return (size_t)stages<D>() * image_bytes<D>() + (size_t)waves<D>() * query_lds_fragments<D, 1>() * 1024;
 }
 
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
@@ -143,62 +136,15 @@ __device__ __forceinline__ floatx16 mfma32(half8 a, half8 b, floatx16 c)
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
 }
 
-// Eight codes of piece idx of a block's code range (8-bit: two u32; 4-bit:
-// one u32; 2-bit: one u16), as the words holding codes 0..3 and 4..7 (the
-// same word unless the codes are 8-bit).
-struct Piece {
-    uint32_t lo, hi;
-};
-
-template <bool W8>
-__device__ __forceinline__ Piece piece(const uint8_t* sec, int idx, int bits)
-{
-    if constexpr (W8) {
-        const u32x2 w = ((const u32x2*)sec)[idx];
-        return Piece{w.x, w.y};
-    }
-    const uint32_t w = bits == 4 ? ((const uint32_t*)sec)[idx] : ((const uint16_t*)sec)[idx];
-    return Piece{w, w};
-}
-
-// Code e (0..7) of a piece.
-__device__ __forceinline__ uint32_t code_of(const Piece& w, int bits, int e)
-{
-    const uint32_t x = e < 4 ? w.lo : w.hi;
-    return (x >> ((bits * e) & 31)) & ((1u << bits) - 1u);
-}
-
-// four consecutive scales or offsets from element i (a multiple of 4)
-__device__ __forceinline__ void meta4(const uint8_t* sec, int i, bool m16, float* v)
-{
-    if (m16) {
-        const uint2 h = *(const uint2*)(sec + 2 * i);
-        v[0] = f16_bits_to_f32((uint16_t)h.x);
-        v[1] = f16_bits_to_f32((uint16_t)(h.x >> 16));
-        v[2] = f16_bits_to_f32((uint16_t)h.y);
-        v[3] = f16_bits_to_f32((uint16_t)(h.y >> 16));
-    } else {
-        const floatx4 a = *(const floatx4*)(sec + 4 * i);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            v[e] = a[e];
-    }
-}
-
-__device__ __forceinline__ float half_bits(const uint16_t* row, size_t i)
-{
-    return f16_bits_to_f32(row[i]);
-}
-
 // Whether a block (sink block when sinkblk, else tail block blk) is a code
-// block: per-token key groups, no rotation, every token of the block coded.
+// block: per-token key groups, no rotation, its tokens coded.
 // Its image holds the key codes as exact fp16 values in place of k_hat's hi
 // half, and the group scales and offsets in place of the lo half.  Groups of
 // 32 at D = 256 (eight groups) keep hi + lo keys.
 template <int D>
 __device__ __forceinline__ bool code_block(const AttnParams& p, bool sinkblk, int blk)
 {
-    return p.k_axis == KVQ_PER_TOKEN && !p.rotate && !(D >= 256 && p.k_group == 32) && !sinkblk && 32 * blk + 31 < p.nq;
+    return p.k_axis == KVQ_PER_TOKEN && !p.rotate && !(D >= 256 && p.k_group == 32) && !sinkblk && 32 * blk < p.nq;
 }
 
 // One block's packed sections (codes, scales, offsets of K and V; offsets
@@ -213,7 +159,7 @@ struct SectionBytes {
 };
 
 template <int D, bool W8>
-__device__ __forceinline__ SectionBytes section_bytes(const AttnParams& p)
+__host__ __device__ __forceinline__ SectionBytes section_bytes(const AttnParams& p)
 {
     const int msz = p.meta16 ? 2 : 4;
     SectionBytes s;
@@ -237,91 +183,90 @@ __device__ __forceinline__ Sections cache_sections(const AttnParams& p, const Se
     return s;
 }
 
-// Rows of the rotation scratch: 32 tokens of D fp32, the pitch padded so that
-// 16-byte reads of one channel chunk over consecutive rows hit distinct banks.
+// Rotation scratch: 8 rows (tokens) of D fp32 per wave, the pitch padded so
+// that 16-byte reads of one channel chunk over consecutive rows hit distinct
+// banks.  A wave rotates its own rows, and a wave's LDS accesses are performed
+// in order, so no barrier is needed.
 template <int D>
-constexpr int scratch_pitch()
+__host__ __device__ constexpr int scratch_pitch()
 {
     return D + 4;
 }
 
 template <int D>
-constexpr size_t scratch_bytes()
+__host__ __device__ constexpr int scratch_bytes()  // of four waves
 {
-    return (size_t)32 * scratch_pitch<D>() * 4;
+    return 4 * 8 * scratch_pitch<D>() * 4;
 }
 
-// In-place FWHT of the scratch's 32 rows (butterflies of half width 1, 2, ..,
-// D / 2), then * c, by a workgroup of NTH threads: three half widths per pass
-// in registers (1, 2, 4; 8, 16, 32; then 64 and 128).  Ends with a barrier.
-template <int D, int NTH>
-__device__ __forceinline__ void fwht_block(float* x, float c)
+template <int N, int FIRST>
+__device__ __forceinline__ void butterflies(float* v)
+{
+#pragma unroll
+    for (int h = FIRST; h < N; h <<= 1)
+#pragma unroll
+        for (int e = 0; e < N; ++e)
+            if (!(e & h)) {
+                const float s = v[e], t = v[e + h];
+                v[e] = s + t;
+                v[e + h] = s - t;
+            }
+}
+
+// The compiler keeps the LDS accesses before and after in this order.
+__device__ __forceinline__ void lds_order()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// In-place FWHT of the wave's 8 rows (butterflies of half width 1, 2, ..,
+// D / 2), then * c: three half widths per pass in registers (1, 2, 4; 8, 16,
+// 32; then 64 and 128).
+template <int D>
+__device__ __forceinline__ void fwht_rows8(float* x, int lane, float c)
 {
     constexpr int PT = scratch_pitch<D>();
-    __syncthreads();
+    lds_order();
 #pragma unroll
-    for (int i = threadIdx.x; i < 32 * (D / 8); i += NTH) {
-        float* r = x + (i & 31) * PT + 8 * (i >> 5);
-        floatx4 a = *(const floatx4*)r, b = *(const floatx4*)(r + 4);
+    for (int i = lane; i < D; i += 64) {
+        float* r = x + (i & 7) * PT + 8 * (i >> 3);
+        const floatx4 a = *(const floatx4*)r, b = *(const floatx4*)(r + 4);
         float v[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-#pragma unroll
-        for (int h = 1; h < 8; h <<= 1)
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (!(e & h)) {
-                    const float s = v[e], t = v[e + h];
-                    v[e] = s + t;
-                    v[e + h] = s - t;
-                }
+        butterflies<8, 1>(v);
         *(floatx4*)r = floatx4{v[0], v[1], v[2], v[3]};
         *(floatx4*)(r + 4) = floatx4{v[4], v[5], v[6], v[7]};
     }
-    __syncthreads();
+    lds_order();
 #pragma unroll
-    for (int i = threadIdx.x; i < 32 * (D / 8); i += NTH) {
-        // lanes: eight channels of a 64-channel span, then spans, then rows
-        float* r = x + (i / (D / 8)) * PT + 64 * ((i % (D / 8)) >> 3) + (i & 7);
+    for (int i = lane; i < D; i += 64) {
+        // lanes: eight channels of a 64-channel span, then rows, then spans
+        float* r = x + ((i >> 3) & 7) * PT + 64 * (i >> 6) + (i & 7);
         float v[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e)
             v[e] = r[8 * e];
-#pragma unroll
-        for (int h = 1; h < 8; h <<= 1)
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (!(e & h)) {
-                    const float s = v[e], t = v[e + h];
-                    v[e] = s + t;
-                    v[e + h] = s - t;
-                }
+        butterflies<8, 1>(v);
 #pragma unroll
         for (int e = 0; e < 8; ++e)
             r[8 * e] = D == 64 ? v[e] * c : v[e];
     }
-    __syncthreads();
+    lds_order();
     if constexpr (D > 64) {
         constexpr int NV = D / 64;
 #pragma unroll
-        for (int i = threadIdx.x; i < 32 * 64; i += NTH) {
-            float* r = x + (i >> 6) * PT + (i & 63);
+        for (int i = 0; i < 8; ++i) {
+            float* r = x + i * PT + lane;
             float v[NV];
 #pragma unroll
             for (int e = 0; e < NV; ++e)
                 v[e] = r[64 * e];
-#pragma unroll
-            for (int h = 1; h < NV; h <<= 1)
-#pragma unroll
-                for (int e = 0; e < NV; ++e)
-                    if (!(e & h)) {
-                        const float s = v[e], t = v[e + h];
-                        v[e] = s + t;
-                        v[e + h] = s - t;
-                    }
+            butterflies<NV, 1>(v);
 #pragma unroll
             for (int e = 0; e < NV; ++e)
                 r[64 * e] = v[e] * c;
         }
-        __syncthreads();
+        lds_order();
     }
 }
 
@@ -330,191 +275,452 @@ __device__ __forceinline__ void fwht_block(float* x, float c)
 // and binary16 must still hold it.
 constexpr float kRotKeyScale = 0.0625f;
 
-// The image of one block, by a workgroup of NTH threads: sink block sb when
-// sb >= 0, else tail block blk.  CODED: every token is coded (and `s` may be
-// in LDS).  Tokens past the end (sink rows beyond n_sink, tail tokens beyond
-// n) are zeros: the causal mask removes them, and zero values keep 0 * v
-// finite.  W8: both code widths are 8 bits.  ROT: through `scratch` (LDS),
-// with barriers; otherwise none.
-template <int D, bool W8, bool ROT, int NTH, bool CODED>
-__device__ __forceinline__ void build_image(const AttnParams& p, int unit, int sb, int blk, const Sections& s, bool ck,
-                                            uint8_t* img, float* scratch)
+// fp32 -> fp16 hi + lo: hi is v with its mantissa cut to binary16 width, lo the
+// exact remainder, each rounded once (22 bits together).
+__device__ __forceinline__ void split_cut8(const float* v, half8* hi, half8* lo)
 {
-    const int kbits = W8 ? 8 : p.k_bits, vbits = W8 ? 8 : p.v_bits;
-    const bool kaff = p.k_mode == KVQ_AFFINE, vaff = p.v_mode == KVQ_AFFINE;
-    const bool m16 = p.meta16 != 0;
-    const size_t sbase = (size_t)unit * p.sink;
-    const size_t rbase = (size_t)unit * p.ring;
+    float h[8], l[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        h[e] = __uint_as_float(__float_as_uint(v[e]) & 0xFFFFE000u);
+        l[e] = v[e] - h[e];
+    }
+    *hi = pack_half8(h);
+    *lo = pack_half8(l);
+}
+
+// Where a rotated block's rows go back to the image: token tau's channels 8 P
+// .. 8 P + 7 of the keys, and channel d of octet wv's values.
+template <int D>
+__device__ __forceinline__ void put_key(uint8_t* img, int tau, int P, const float* x)
+{
+    half8 h, l;
+    split_cut8(x, &h, &l);
+    *(u32x4*)(img + 512 * P + 16 * tau) = __builtin_bit_cast(u32x4, h);
+    *(u32x4*)(img + klo_at<D>() + 512 * P + 16 * tau) = __builtin_bit_cast(u32x4, l);
+}
+
+template <int D>
+__device__ __forceinline__ void rotate_keys(const AttnParams& p, uint8_t* img, float* rows, int wv, int lane)
+{
     constexpr int PT = scratch_pitch<D>();
-
-    // K piece: token tau, channels 8 P .. 8 P + 7; 32 consecutive lanes write
-    // 512 contiguous bytes
+    fwht_rows8<D>(rows, lane, p.rot_c * kRotKeyScale);
 #pragma unroll
-    for (int pc = threadIdx.x; pc < 4 * D; pc += NTH) {
-        const int tau = pc & 31, P = pc >> 5;
-        float x[8];
-        const uint16_t* row = nullptr;  // fp16 source row (sink or window)
-        bool coded = CODED;
-        if constexpr (!CODED) {
-            if (sb >= 0) {
-                const int ts = 32 * sb + tau;
-                if (ts < p.n_sink)
-                    row = p.kq + (sbase + ts) * D;
-            } else {
-                const int t = 32 * blk + tau;
-                if (t < p.nq)
-                    coded = true;
-                else if (t < p.n)
-                    row = p.kr + (rbase + t % p.ring) * D;
-            }
-        }
-        if (coded) {
-            const int r = 4 * (tau >> 3) + (tau & 3), half = (tau >> 2) & 1;
-            const int idx = (half * 64 + r + 16 * (P & 3)) * (D / 32) + (P >> 2);
-            const Piece w = piece<W8>(s.kc, idx, kbits);
-            if (!ROT && ck) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    x[e] = (float)code_of(w, kbits, e);
-            } else if (p.k_axis == KVQ_PER_TOKEN) {
-                const int mi = ((8 * P) / p.k_group) * 32 + tau;
-                const float sc = meta(s.ks, mi, m16), z = kaff ? meta(s.kz, mi, m16) : 0.0f;
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    x[e] = dq(p.k_mode, kbits, code_of(w, kbits, e), sc, z);
-            } else {
-                // per-channel keys: the piece's eight channels' scales
-                // (and offsets) are consecutive, two vector loads each
-                float sc[8], zc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                meta4(s.ks, 8 * P, m16, sc);
-                meta4(s.ks, 8 * P + 4, m16, sc + 4);
-                if (kaff) {
-                    meta4(s.kz, 8 * P, m16, zc);
-                    meta4(s.kz, 8 * P + 4, m16, zc + 4);
-                }
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    x[e] = dq(p.k_mode, kbits, code_of(w, kbits, e), sc[e], zc[e]);
-            }
-        } else if (row) {
-            const u32x4 rw = *(const u32x4*)(row + 8 * P);
-            const uint32_t w4[4] = {rw.x, rw.y, rw.z, rw.w};
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                x[e] = f16_bits_to_f32((uint16_t)(w4[e >> 1] >> (16 * (e & 1))));
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                x[e] = 0.0f;
-        }
-        if constexpr (ROT) {
-            float* dst = scratch + tau * PT + 8 * P;
-            *(floatx4*)dst = floatx4{x[0], x[1], x[2], x[3]};
-            *(floatx4*)(dst + 4) = floatx4{x[4], x[5], x[6], x[7]};
-        } else if (ck) {
-            *(u32x4*)(img + 16 * pc) = __builtin_bit_cast(u32x4, pack_half8(x));
-        } else {
-            half8 h, l;
-            split_half8(x, &h, &l);
-            *(u32x4*)(img + 16 * pc) = __builtin_bit_cast(u32x4, h);
-            *(u32x4*)(img + klo_at<D>() + 16 * pc) = __builtin_bit_cast(u32x4, l);
-        }
+    for (int i = lane; i < D; i += 64) {
+        const float* src = rows + (i & 7) * PT + 8 * (i >> 3);
+        const floatx4 a = *(const floatx4*)src, b = *(const floatx4*)(src + 4);
+        const float x[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+        put_key<D>(img, 8 * wv + (i & 7), i >> 3, x);
     }
-    if constexpr (ROT) {
-        fwht_block<D, NTH>(scratch, p.rot_c * kRotKeyScale);
-#pragma unroll
-        for (int pc = threadIdx.x; pc < 4 * D; pc += NTH) {
-            const float* src = scratch + (pc & 31) * PT + 8 * (pc >> 5);
-            const floatx4 a = *(const floatx4*)src, b = *(const floatx4*)(src + 4);
-            const float x[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-            half8 h, l;
-            split_half8(x, &h, &l);
-            *(u32x4*)(img + 16 * pc) = __builtin_bit_cast(u32x4, h);
-            *(u32x4*)(img + klo_at<D>() + 16 * pc) = __builtin_bit_cast(u32x4, l);
-        }
-        __syncthreads();  // the values follow through the same scratch
-    }
+    lds_order();  // the values follow through the same rows
+}
 
-    // V piece: channel d, fragment chunk c = 2 u + h (tokens 16 u + 4 h + {0
-    // .. 3, 8 .. 11}: codes 4 h .. 4 h + 3 of octets 2 u and 2 u + 1)
+template <int D>
+__device__ __forceinline__ void rotate_values(const AttnParams& p, uint8_t* img, float* rows, int wv, int lane)
+{
+    constexpr int PT = scratch_pitch<D>();
+    fwht_rows8<D>(rows, lane, p.rot_c);
 #pragma unroll
-    for (int pc = threadIdx.x; pc < 4 * D; pc += NTH) {
-        const int d = (pc & 31) + 32 * (pc >> 7), c = (pc >> 5) & 3, u = c >> 1, h = c & 1;
+    for (int d = lane; d < D; d += 64) {
         float x[8];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int tk0 = 16 * u + 8 * j + 4 * h;  // first of four tokens
-            if (CODED || (sb < 0 && 32 * blk + tk0 < p.nq)) {
-                const Piece w = piece<W8>(s.vc, (d % 16 + 16 * (2 * u + j)) * (D / 16) + d / 16, vbits);
-                const int mi = (d / p.v_group) * 32 + tk0;
-                float sc[4], zc[4] = {0.f, 0.f, 0.f, 0.f};
-                meta4(s.vs, mi, m16, sc);
-                if (vaff)
-                    meta4(s.vz, mi, m16, zc);
+        for (int e = 0; e < 8; ++e)
+            x[e] = rows[e * PT + d];
+        const u32x4 v = __builtin_bit_cast(u32x4, pack_half8(x));
+        // octet wv is half wv % 2 of fragment chunks 2 (wv / 2) + {0, 1}
+        uint8_t* dst = img + vt_at<D>() + 2048 * (d >> 5) + 1024 * (wv >> 1) + 16 * (d & 31) + 8 * (wv & 1);
+        *(u32x2*)dst = u32x2{v.x, v.y};
+        *(u32x2*)(dst + 512) = u32x2{v.z, v.w};
+    }
+    lds_order();
+}
+
+// ---- Images are built by four waves (tid 0 .. 255) without barriers, by block
+// kind: a tail block of coded tokens, or one of fp16 rows (window or sink; the
+// two never mix, since windows are coded 32 tokens at a time).  Tokens past the
+// end are masked in the scores whatever their keys hold, and get zero values
+// (0 times anything stored there must stay 0).
+//
+// Coded blocks.  The widths, the metadata type and the key axis are
+// compile-time and their choice is made once per block: with them as run-time
+// branches around every piece, a block took 6000 cycles (LDS latencies in
+// series), three times its products.
+
+// Eight codes as floats.  Conversions run at a quarter of the vector rate, so
+// a byte of codes becomes the low mantissa byte of 2^23 (one permute) and 2^23
+// is subtracted: exact, two full-rate operations.
+template <int BITS>
+struct Codes {
+    uint32_t w[BITS == 8 ? 2 : 1];
+};
+
+template <int BITS>
+__device__ __forceinline__ Codes<BITS> load_codes(const uint8_t* sec, int idx)
+{
+    Codes<BITS> c;
+    if constexpr (BITS == 8) {
+        const u32x2 v = ((const u32x2*)sec)[idx];
+        c.w[0] = v.x;
+        c.w[1] = v.y;
+    } else if constexpr (BITS == 4) {
+        c.w[0] = ((const uint32_t*)sec)[idx];
+    } else {
+        c.w[0] = ((const uint16_t*)sec)[idx];
+    }
+    return c;
+}
+
+__device__ __forceinline__ float byte_f32(uint32_t w, int k)
+{
+    return __uint_as_float(__builtin_amdgcn_perm(0x4B000000u, w, 0x070c0c00u | (uint32_t)k)) - 8388608.0f;
+}
+
+template <int BITS>
+__device__ __forceinline__ void codes_f32(const Codes<BITS>& c, float* x)
+{
+    if constexpr (BITS == 8) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float val = dq(p.v_mode, vbits, code_of(w, vbits, 4 * h + e), sc[e], zc[e]);
-                    if constexpr (CODED) {
-                        x[4 * j + e] = val;
-                    } else {
-                        const int t = 32 * blk + tk0 + e;
-                        x[4 * j + e] = t < p.nq  ? val
-                                       : t < p.n ? half_bits(p.vr, (rbase + t % p.ring) * D + d)
-                                                 : 0.0f;
-                    }
-                }
-            } else {
+        for (int e = 0; e < 8; ++e)
+            x[e] = byte_f32(c.w[e >> 2], e & 3);
+    } else if constexpr (BITS == 4) {
+        const uint32_t a = c.w[0] & 0x0F0F0F0Fu, b = (c.w[0] >> 4) & 0x0F0F0F0Fu;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int tk = tk0 + e;
-                    float val = 0.0f;
-                    if (sb >= 0) {
-                        const int ts = 32 * sb + tk;
-                        if (ts < p.n_sink)
-                            val = half_bits(p.vq, (sbase + ts) * D + d);
-                    } else {
-                        const int t = 32 * blk + tk;
-                        if (t < p.n)
-                            val = half_bits(p.vr, (rbase + t % p.ring) * D + d);
-                    }
-                    x[4 * j + e] = val;
-                }
-            }
+        for (int e = 0; e < 4; ++e) {
+            x[2 * e] = byte_f32(a, e);
+            x[2 * e + 1] = byte_f32(b, e);
         }
-        if constexpr (ROT) {
+    } else {
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-                scratch[(16 * u + 4 * h + 8 * (e >> 2) + (e & 3)) * PT + d] = x[e];
-        } else {
-            *(u32x4*)(img + vt_at<D>() + 16 * pc) = __builtin_bit_cast(u32x4, pack_half8(x));
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t a = (c.w[0] >> (2 * e)) & 0x0303u;
+            x[e] = byte_f32(a, 0);
+            x[e + 4] = byte_f32(a, 1);
         }
     }
-    if constexpr (ROT) {
-        fwht_block<D, NTH>(scratch, p.rot_c);
+}
+
+// N (4 or 8) consecutive scales or offsets from element i (a multiple of 4).
+template <bool M16, int N>
+__device__ __forceinline__ void meta_n(const uint8_t* sec, int i, float* v)
+{
 #pragma unroll
-        for (int pc = threadIdx.x; pc < 4 * D; pc += NTH) {
-            const int d = (pc & 31) + 32 * (pc >> 7), c = (pc >> 5) & 3;
+    for (int k = 0; k < N; k += 4) {
+        if constexpr (M16) {
+            const u32x2 h = *(const u32x2*)(sec + 2 * (i + k));
+            v[k] = f16_bits_to_f32((uint16_t)h.x);
+            v[k + 1] = f16_bits_to_f32((uint16_t)(h.x >> 16));
+            v[k + 2] = f16_bits_to_f32((uint16_t)h.y);
+            v[k + 3] = f16_bits_to_f32((uint16_t)(h.y >> 16));
+        } else {
+            const floatx4 a = *(const floatx4*)(sec + 4 * (i + k));
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                v[k + e] = a[e];
+        }
+    }
+}
+
+template <bool M16>
+__device__ __forceinline__ float meta_1(const uint8_t* sec, int i)
+{
+    if constexpr (M16)
+        return f16_bits_to_f32(((const uint16_t*)sec)[i]);
+    else
+        return ((const float*)sec)[i];
+}
+
+// Keys of a coded block, loads first: the
+// compiler cannot tell the image's stores from the packed block's loads in
+// LDS, so loads left beside their use would wait for each other.
+// CK: a code block's exact codes, scales and offsets.  A reconstructed element
+// is fma(c, s, z'), z' = z for affine codes and -2^(BITS - 1) s (exact) for
+// symmetric ones, which is (c - 2^(BITS - 1)) s rounded once.
+template <int D, int BITS, bool M16, bool AFF, bool PERCH, bool CK, bool ROT>
+struct Keys {
+    static constexpr int N = 4 * D / 256, NM = CK ? 1 : N, W = PERCH ? 8 : 1, PT = scratch_pitch<D>();
+    Codes<BITS> c[N];
+    float sc[NM][W], z[NM][W];
+
+    // piece i of a thread: token tau, channels 8 P .. 8 P + 7 (a rotating wave
+    // takes its own eight tokens)
+    static __device__ __forceinline__ int tau(int tid) { return ROT ? 8 * (tid >> 6) + (tid & 7) : tid & 31; }
+    static __device__ __forceinline__ int chunk(int tid, int i) { return (ROT ? (tid & 63) >> 3 : tid >> 5) + 8 * i; }
+
+    __device__ __forceinline__ void load(const AttnParams& p, const Sections& s, int tid)
+    {
+        const uint8_t* sz = AFF || p.k_mode == KVQ_AFFINE ? s.kz : s.ks;  // symmetric: any readable address
+        const int lg = PERCH ? 0 : 31 - __builtin_clz(p.k_group), t = tau(tid);
+        const int r = 4 * (t >> 3) + (t & 3), half = (t >> 2) & 1;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int P = chunk(tid, i);
+            c[i] = load_codes<BITS>(s.kc, (half * 64 + r + 16 * (P & 3)) * (D / 32) + (P >> 2));
+            if constexpr (CK) {
+                continue;
+            } else if constexpr (PERCH) {
+                meta_n<M16, 8>(s.ks, 8 * P, sc[i]);
+                meta_n<M16, 8>(sz, 8 * P, z[i]);
+            } else {
+                const int mi = ((8 * P) >> lg) * 32 + t;
+                sc[i][0] = meta_1<M16>(s.ks, mi);
+                z[i][0] = meta_1<M16>(sz, mi);
+            }
+        }
+    }
+
+    __device__ __forceinline__ void finish(const AttnParams& p, const Sections& s, uint8_t* img, float* scratch, int tid)
+    {
+        const bool aff = AFF || p.k_mode == KVQ_AFFINE;
+        constexpr float nh = -(float)(1 << (BITS - 1));
+        const int lane = tid & 63, wv = tid >> 6, t = tau(tid);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int P = chunk(tid, i);
             float x[8];
+            codes_f32<BITS>(c[i], x);
+            if constexpr (CK) {
+                *(u32x4*)(img + 512 * P + 16 * t) = __builtin_bit_cast(u32x4, pack_half8(x));
+                continue;
+            }
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-                x[e] = scratch[(16 * (c >> 1) + 4 * (c & 1) + 8 * (e >> 2) + (e & 3)) * PT + d];
-            *(u32x4*)(img + vt_at<D>() + 16 * pc) = __builtin_bit_cast(u32x4, pack_half8(x));
+            for (int e = 0; e < 8; ++e) {
+                const int k = PERCH ? e : 0, m = CK ? 0 : i;
+                x[e] = fmaf(x[e], sc[m][k], aff ? z[m][k] : nh * sc[m][k]);
+            }
+            if constexpr (ROT) {
+                float* dst = scratch + t * PT + 8 * P;
+                *(floatx4*)dst = floatx4{x[0], x[1], x[2], x[3]};
+                *(floatx4*)(dst + 4) = floatx4{x[4], x[5], x[6], x[7]};
+            } else {
+                put_key<D>(img, t, P, x);
+            }
+        }
+        if constexpr (ROT)
+            rotate_keys<D>(p, img, scratch + wv * 8 * PT, wv, lane);
+        if constexpr (CK) {
+            // The scales (fp32, in place of the lo half) are kept as ratios
+            // s[g] / s[g + 1], the last group's as it is: the score sum over
+            // groups is then one chain of products, its running sum moved from
+            // one group's scale to the next (scales are never zero: the code's
+            // floor is 1e-8, 2^-24 in fp16).  Then the offsets z'.
+            const int n = 32 * (D >> (31 - __builtin_clz(p.k_group)));
+            const uint8_t* sz = aff ? s.kz : s.ks;
+            float* ms = (float*)(img + klo_at<D>());
+            for (int i = tid; i < n; i += 256) {
+                const float s0 = meta_1<M16>(s.ks, i), z0 = meta_1<M16>(sz, i);
+                ms[i] = i + 32 < n ? s0 / meta_1<M16>(s.ks, i + 32) : s0;
+                ms[n + i] = aff ? z0 : nh * s0;
+            }
         }
     }
-    // a code block's key scales and offsets z'[g][t] (fp32, in place of the
-    // lo half), with k_hat = c s + z': z' = z for affine codes, -2^(bits-1) s
-    // for symmetric ones.  The scales are kept as ratios s[g] / s[g + 1], the
-    // last group's as it is: the score sum over groups is then one chain of
-    // products, its running sum moved from one group's scale to the next
-    // (scales are never zero: the code's floor is 1e-8, 2^-24 in fp16).
-    if (!ROT && ck) {
-        const int ng = D / p.k_group;
-        float* ms = (float*)(img + klo_at<D>());
-        for (int i = threadIdx.x; i < 32 * ng; i += NTH) {
-            const float sc = meta(s.ks, i, m16);
-            ms[i] = i + 32 < 32 * ng ? sc / meta(s.ks, i + 32, m16) : sc;
-            ms[32 * ng + i] = kaff ? meta(s.kz, i, m16) : -(float)(1 << (kbits - 1)) * sc;
+};
+
+// Values of a coded block, the first `valid` tokens live.  Wave wv takes fragment chunk wv = 2 u + h:
+// codes 4 h .. 4 h + 3 of octets 2 u and 2 u + 1 (a rotating wave octet wv).
+template <int D, int BITS, bool M16, bool AFF, bool ROT>
+struct Values {
+    static constexpr int N = D / 64, PT = scratch_pitch<D>();
+    Codes<BITS> c[N][ROT ? 1 : 2];
+    float sc[N][8], z[N][8];
+
+    __device__ __forceinline__ void load(const AttnParams& p, const Sections& s, int tid)
+    {
+        const uint8_t* sz = AFF || p.v_mode == KVQ_AFFINE ? s.vz : s.vs;
+        const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), u = wv >> 1, h = wv & 1;
+        const int lg = 31 - __builtin_clz(p.v_group);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int d = lane + 64 * i, at = d % 16 * (D / 16) + d / 16, mg = (d >> lg) * 32;
+            if constexpr (ROT) {
+                c[i][0] = load_codes<BITS>(s.vc, at + 16 * wv * (D / 16));
+                meta_n<M16, 8>(s.vs, mg + 8 * wv, sc[i]);
+                meta_n<M16, 8>(sz, mg + 8 * wv, z[i]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    c[i][j] = load_codes<BITS>(s.vc, at + 16 * (2 * u + j) * (D / 16));
+                    meta_n<M16, 4>(s.vs, mg + 16 * u + 8 * j + 4 * h, sc[i] + 4 * j);
+                    meta_n<M16, 4>(sz, mg + 16 * u + 8 * j + 4 * h, z[i] + 4 * j);
+                }
+            }
         }
+    }
+
+    __device__ __forceinline__ void finish(const AttnParams& p, int valid, uint8_t* img, float* scratch, int tid)
+    {
+        const bool aff = AFF || p.v_mode == KVQ_AFFINE;
+        constexpr float nh = -(float)(1 << (BITS - 1));
+        const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = wv & 1;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int d = lane + 64 * i;
+            float x[8];
+            if constexpr (ROT) {
+                codes_f32<BITS>(c[i][0], x);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    // the codes of four tokens at the bottom (8-bit: in one word)
+                    const uint32_t w0 = c[i][j].w[0], w1 = c[i][j].w[BITS == 8];
+                    const uint32_t w = BITS == 8 ? w0 ^ ((w0 ^ w1) & (uint32_t)-h) : w0 >> (4 * BITS * h);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        x[4 * j + e] = BITS == 8   ? byte_f32(w, e)
+                                       : BITS == 4 ? byte_f32((e & 1) ? (w >> 4) & 0x0F0Fu : w & 0x0F0Fu, e >> 1)
+                                                   : byte_f32((w >> (2 * e)) & 3u, 0);
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                x[e] = fmaf(x[e], sc[i][e], aff ? z[i][e] : nh * sc[i][e]);
+            if (valid < 32) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    x[e] = (ROT ? 8 * wv + e : 16 * (wv >> 1) + 4 * h + 8 * (e >> 2) + (e & 3)) < valid ? x[e] : 0.0f;
+            }
+            if constexpr (ROT) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    scratch[(wv * 8 + e) * PT + d] = x[e];
+            } else {
+                *(u32x4*)(img + vt_at<D>() + 2048 * (d >> 5) + 512 * wv + 16 * (d & 31)) =
+                    __builtin_bit_cast(u32x4, pack_half8(x));
+            }
+        }
+        if constexpr (ROT)
+            rotate_values<D>(p, img, scratch + wv * 8 * PT, wv, lane);
+    }
+};
+
+// The image of a coded block; CK as code_block says.
+template <int D, int KB, int VB, bool M16, bool AFF, bool PERCH, bool CK, bool ROT>
+__device__ __forceinline__ void coded_blocks(const AttnParams& p, const Sections& s, int valid, uint8_t* img, float* scratch, int tid)
+{
+    Keys<D, KB, M16, AFF, PERCH, CK, ROT> k;
+    Values<D, VB, M16, AFF, ROT> v;
+    k.load(p, s, tid);
+    v.load(p, s, tid);
+    k.finish(p, s, img, scratch, tid);
+    v.finish(p, valid, img, scratch, tid);
+}
+
+template <int D, int KB, int VB, bool M16, bool AFF, bool CK, bool ROT>
+__device__ __forceinline__ void coded_axis(const AttnParams& p, const Sections& s, int valid, uint8_t* img, float* scratch, int tid)
+{
+    if constexpr (CK) {
+        coded_blocks<D, KB, VB, M16, AFF, false, true, false>(p, s, valid, img, scratch, tid);
+    } else {
+        if (p.k_axis == KVQ_PER_CHANNEL)
+            coded_blocks<D, KB, VB, M16, AFF, true, false, ROT>(p, s, valid, img, scratch, tid);
+        else if constexpr (ROT || D == 256)  // (other per-token keys are code blocks)
+            coded_blocks<D, KB, VB, M16, AFF, false, false, ROT>(p, s, valid, img, scratch, tid);
+    }
+}
+
+template <int D, bool W8, bool M16, bool AFF, bool CK, bool ROT>
+__device__ __forceinline__ void coded_bits(const AttnParams& p, const Sections& s, int valid, uint8_t* img, float* scratch, int tid)
+{
+    if constexpr (W8) {
+        coded_axis<D, 8, 8, M16, AFF, CK, ROT>(p, s, valid, img, scratch, tid);
+    } else if (p.k_bits == 4) {
+        if (p.v_bits == 4)
+            coded_axis<D, 4, 4, M16, AFF, CK, ROT>(p, s, valid, img, scratch, tid);
+        else
+            coded_axis<D, 4, 2, M16, AFF, CK, ROT>(p, s, valid, img, scratch, tid);
+    } else {
+        if (p.v_bits == 4)
+            coded_axis<D, 2, 4, M16, AFF, CK, ROT>(p, s, valid, img, scratch, tid);
+        else
+            coded_axis<D, 2, 2, M16, AFF, CK, ROT>(p, s, valid, img, scratch, tid);
+    }
+}
+
+template <int D, bool W8, bool CK, bool ROT>
+__device__ __forceinline__ void coded_image(const AttnParams& p, const Sections& s, int valid, uint8_t* img, float* scratch,
+                                            int tid)
+{
+    if (p.meta16)
+        coded_bits<D, W8, true, false, CK, ROT>(p, s, valid, img, scratch, tid);
+    else if (p.k_mode == KVQ_AFFINE && p.v_mode == KVQ_AFFINE)
+        coded_bits<D, W8, false, true, CK, ROT>(p, s, valid, img, scratch, tid);
+    else
+        coded_bits<D, W8, false, false, CK, ROT>(p, s, valid, img, scratch, tid);
+}
+
+// The image of a block of fp16 rows: token i is row (first + i) % ring of kr, vr
+// [.][D], the first `valid` tokens live.  All loads first, as above.
+template <int D, bool ROT>
+__device__ __forceinline__ void fp16_image(const AttnParams& p, const uint16_t* kr, const uint16_t* vr, int first, int ring,
+                                           int valid, uint8_t* img, float* scratch, int tid)
+{
+    constexpr int N = 4 * D / 256, NV = D / 64, PT = scratch_pitch<D>();
+    using K = Keys<D, 2, false, false, false, true, ROT>;
+    const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), t = K::tau(tid);
+    u32x4 kw[N];
+    uint16_t vw[NV][8];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        kw[i] = u32x4{0u, 0u, 0u, 0u};
+        if (t < valid)
+            kw[i] = *(const u32x4*)(kr + (size_t)((first + t) % ring) * D + 8 * K::chunk(tid, i));
+    }
+    int row[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int tok = ROT ? 8 * wv + e : 16 * (wv >> 1) + 4 * (wv & 1) + 8 * (e >> 2) + (e & 3);
+        row[e] = tok < valid ? (first + tok) % ring : -1;
+    }
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            vw[i][e] = row[e] >= 0 ? vr[(size_t)row[e] * D + lane + 64 * i] : (uint16_t)0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int P = K::chunk(tid, i);
+        if constexpr (ROT) {
+            const uint32_t w[4] = {kw[i].x, kw[i].y, kw[i].z, kw[i].w};
+            float* dst = scratch + t * PT + 8 * P;
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                dst[e] = f16_bits_to_f32((uint16_t)(w[e >> 1] >> (16 * (e & 1))));
+        } else {
+            *(u32x4*)(img + 512 * P + 16 * t) = kw[i];
+            *(u32x4*)(img + klo_at<D>() + 512 * P + 16 * t) = u32x4{0u, 0u, 0u, 0u};
+        }
+    }
+    if constexpr (ROT)
+        rotate_keys<D>(p, img, scratch + wv * 8 * PT, wv, lane);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int d = lane + 64 * i;
+        if constexpr (ROT) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                scratch[(wv * 8 + e) * PT + d] = f16_bits_to_f32(vw[i][e]);
+        } else {
+            u32x4 v;
+            v.x = vw[i][0] | ((uint32_t)vw[i][1] << 16);
+            v.y = vw[i][2] | ((uint32_t)vw[i][3] << 16);
+            v.z = vw[i][4] | ((uint32_t)vw[i][5] << 16);
+            v.w = vw[i][6] | ((uint32_t)vw[i][7] << 16);
+            *(u32x4*)(img + vt_at<D>() + 2048 * (d >> 5) + 512 * wv + 16 * (d & 31)) = v;
+        }
+    }
+    if constexpr (ROT)
+        rotate_values<D>(p, img, scratch + wv * 8 * PT, wv, lane);
+}
+
+// fp16_image of sink block sb (sb >= 0), or of the window's tail block blk.
+template <int D, bool ROT>
+__device__ __forceinline__ void rows_image(const AttnParams& p, int unit, int sb, int blk, uint8_t* img, float* scratch, int tid)
+{
+    if (sb >= 0) {
+        const size_t at = (size_t)unit * p.sink * D;
+        fp16_image<D, ROT>(p, p.kq + at, p.vq + at, 32 * sb, p.sink, p.n_sink - 32 * sb, img, scratch, tid);
+    } else {
+        const size_t at = (size_t)unit * p.ring * D;
+        fp16_image<D, ROT>(p, p.kr + at, p.vr + at, 32 * blk, p.ring, p.n - 32 * blk, img, scratch, tid);
     }
 }
 
@@ -532,8 +738,13 @@ __global__ __launch_bounds__(kDqThreads) void dequant_kernel(AttnParams p)
     const int blk = v - p.pf_nsb;
     const size_t i = (size_t)unit * (p.T >> 5) + (sinkblk ? 0 : blk);
     const Sections s = cache_sections(p, section_bytes<D, W8>(p), i);
-    build_image<D, W8, ROT, kDqThreads, false>(p, unit, sinkblk ? v : -1, blk, s, code_block<D>(p, sinkblk, blk), img,
-                                               dq_scratch);
+    const int valid = min(32, p.nq - 32 * blk);
+    if (sinkblk || valid <= 0)
+        rows_image<D, ROT>(p, unit, sinkblk ? v : -1, blk, img, dq_scratch, threadIdx.x);
+    else if (!ROT && code_block<D>(p, false, blk))
+        coded_image<D, W8, !ROT, ROT>(p, s, valid, img, dq_scratch, threadIdx.x);
+    else
+        coded_image<D, W8, false, ROT>(p, s, valid, img, dq_scratch, threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -590,7 +801,7 @@ __device__ __forceinline__ void ring_sync(int after)
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// Query rows of a workgroup: rows r0 .. r0 + 255 of a unit.  Positions are
+// Query rows of a workgroup: rows r0 .. r0 + per - 1 of a unit.  Positions are
 // tail indices (token minus sink); sink tokens sit at -sink .. -1, so a chunk
 // that starts in the sink has negative positions.
 struct Tile {
@@ -599,15 +810,15 @@ struct Tile {
     int nsb, nvis;   // sink blocks and all blocks that hold a visible token
 };
 
-__device__ __forceinline__ Tile make_tile(const AttnParams& p, int unit, int tile)
+__device__ __forceinline__ Tile make_tile(const AttnParams& p, int unit, int tile, int per)
 {
     Tile t;
     t.unit = unit;
     t.b = __builtin_amdgcn_readfirstlane(unit / p.H);
     t.h = unit - t.b * p.H;
     t.rows = p.C * p.G;
-    t.r0 = tile * kRows;
-    const int newest = __builtin_amdgcn_readfirstlane(p.n - p.C + (min(t.r0 + kRows, t.rows) - 1) / p.G);
+    t.r0 = tile * per;
+    const int newest = __builtin_amdgcn_readfirstlane(p.n - p.C + (min(t.r0 + per, t.rows) - 1) / p.G);
     const int nkb = newest >= 0 ? newest / 32 + 1 : 0;  // coded-tail blocks
     t.nsb = min((p.n_sink + 31) >> 5, (newest + p.sink) / 32 + 1);
     t.nvis = t.nsb + nkb;
@@ -628,7 +839,7 @@ struct Wave {
     static constexpr int PF = D == 256 ? 3 : 4;  // fragments read ahead (LDS latency)
         // The last QL query fragments of a wave live in LDS (the 16 KiB that the
     // ring leaves free at D = 256, where the registers do not hold them all).
-    static constexpr int QL = query_lds_fragments<D>();
+    static constexpr int QL = query_lds_fragments<D, KG>();
     half8 q[QT][NK - QL];
     uint8_t* ql;
     float qz[QT][NZ];  // lane (col, h): the query's sum over group 2 j + h
@@ -804,11 +1015,13 @@ struct Wave {
         const int hf = lane >> 5;
         const uint8_t* fb = img + 16 * lane;
         auto frag = [&](int at) { return __builtin_bit_cast(half8, *(const u32x4*)(fb + at)); };
+        // step k: channel tile k % NT, token half k / NT
+        auto vfrag = [](int k) { return vt_at<D>() + 1024 * (2 * (k % NT) + k / NT); };
         // the first value fragments, read while the softmax runs
         half8 vf[PF];
 #pragma unroll
         for (int k = 0; k < PF; ++k)
-            vf[k] = frag(vt_at<D>() + 1024 * k);
+            vf[k] = frag(vfrag(k));
         if constexpr (D == 256)
             __builtin_amdgcn_s_setprio(0);
         // ---- online softmax per query column; P^T operands
@@ -877,16 +1090,17 @@ struct Wave {
         for (int k = 0; k < 2 * NT; ++k) {
 #pragma unroll
             for (int c = 0; c < QT; ++c)
-                acc[c][k / 2] = mfma32(vf[k % PF], ph[c][k & 1], acc[c][k / 2]);
+                acc[c][k % NT] = mfma32(vf[k % PF], ph[c][k / NT], acc[c][k % NT]);
             if (k + PF < 2 * NT)
-                vf[k % PF] = frag(vt_at<D>() + 1024 * (k + PF));
+                vf[k % PF] = frag(vfrag(k + PF));
             __builtin_amdgcn_sched_barrier(0);
         }
     }
 
     // Outputs (values were rotated back in the images: outputs are in the
     // original basis for every format): normalized to O, or with several key
-    // ranges per tile this range's unnormalized partial and its (max, sum).
+    // ranges per tile this range's unnormalized partial (the first range's to
+    // O, the others' to part_o [unit][S - 1][rows][D]) and its (max, sum).
     __device__ __forceinline__ void finish(const AttnParams& p, const Tile& t, int split, int wave, int lane)
     {
         const int col = lane & 31, hf = lane >> 5;
@@ -897,15 +1111,15 @@ struct Wave {
             if (R >= t.rows)
                 continue;
             float mul = 1.0f;
-            float* dst;
+            float* dst = p.out + (((size_t)t.b * p.C + R / p.G) * p.H_q + (size_t)t.h * p.G + R % p.G) * D;
             if (p.S_tot == 1) {
                 mul = l > 0.0f ? 1.0f / l : 0.0f;
-                dst = p.out + (((size_t)t.b * p.C + R / p.G) * p.H_q + (size_t)t.h * p.G + R % p.G) * D;
             } else {
-                const size_t at = ((size_t)(t.unit - p.pf_u0) * p.S_tot + split) * t.rows + R;
-                dst = p.part_o + at * D;
+                const size_t uloc = t.unit - p.pf_u0;
+                if (split > 0)
+                    dst = p.part_o + ((uloc * (p.S_tot - 1) + split - 1) * t.rows + R) * D;
                 if (hf == 0)
-                    *(float2*)(p.part_ml + 2 * at) = make_float2(m[c], l);
+                    *(float2*)(p.part_ml + 2 * ((uloc * p.S_tot + split) * t.rows + R)) = make_float2(m[c], l);
             }
 #pragma unroll
             for (int j = 0; j < NT; ++j)
@@ -925,10 +1139,11 @@ __device__ __forceinline__ int xcd_item()
     return (W & 7) == 0 ? (blockIdx.x & 7) * (W >> 3) + (blockIdx.x >> 3) : blockIdx.x;
 }
 
-template <int D, int KG>
-__global__ __launch_bounds__(threads<D>(), 2) void attn_kernel(AttnParams p)
+// NW waves per workgroup, 32 QT NW query rows per tile.
+template <int D, int KG, int NW>
+__global__ __launch_bounds__(64 * NW, D == 256 && NW == 4 ? 1 : 2) void attn_kernel(AttnParams p)
 {
-    constexpr int NW = waves<D>(), QT = qtiles<D>();
+    constexpr int QT = qtiles<D>();
     constexpr int BI = image_bytes<D>(), NST = stages<D>();
     constexpr int CW = BI / 1024 / NW;  // 1 KiB copies of an image per wave
     static_assert(CW * 1024 * NW == BI && CW <= D / 16, "whole copies, one beside a K fragment");
@@ -938,7 +1153,7 @@ __global__ __launch_bounds__(threads<D>(), 2) void attn_kernel(AttnParams p)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // the longest (newest) tiles of a unit start first
     const int L = xcd_item(), uloc = __builtin_amdgcn_readfirstlane(L / p.pf_tiles);
-    const Tile t = make_tile(p, p.pf_u0 + uloc, p.pf_tiles - 1 - (L - uloc * p.pf_tiles));
+    const Tile t = make_tile(p, p.pf_u0 + uloc, p.pf_tiles - 1 - (L - uloc * p.pf_tiles), 32 * QT * NW);
     Wave<D, KG, QT> w;
     w.init(p, t, plds + NST * BI, wave, lane);
 
@@ -988,14 +1203,257 @@ __global__ __launch_bounds__(threads<D>(), 2) void attn_kernel(AttnParams p)
     w.finish(p, t, 0, wave, lane);
 }
 
-template <int D>
-void (*pick(int kg))(AttnParams)
+// ---------------------------------------------------------------------------
+// 3. The fused path: packed blocks through an LDS ring, reconstructed there
+// one block ahead of the one being multiplied.  Eight waves: waves 0 .. 3 (one
+// per SIMD) multiply, 32 query rows each, waves 4 .. 7 copy and reconstruct, so
+// that each SIMD always has vector work beside its matrix products and the
+// reconstruction needs none of the accumulators' registers (done by the
+// multiplying waves themselves it spilled 80 to 116 registers at D = 256).
+// Work item (unit, key range, query tile of 128 rows); key range `split` takes
+// blocks [nvis split / S, nvis (split + 1) / S) of its tile.
+constexpr int kFusedRows = 128, kFusedThreads = 512;
+
+// raw blocks in flight or being reconstructed
+template <int D, bool W8, bool ROT>
+__host__ __device__ constexpr int raw_slots()
 {
-    return kg == 1   ? attn_kernel<D, (D >= 256 ? 0 : 1)>
-           : kg == 2 ? attn_kernel<D, 2>
-           : kg == 4 ? attn_kernel<D, (D >= 128 ? 4 : 1)>
-           : kg == 8 ? attn_kernel<D, (D >= 256 ? 8 : 1)>
-                     : attn_kernel<D, 0>;
+    return D == 256 && (W8 || ROT) ? 2 : 3;
+}
+
+// LDS bytes of one packed block: codes, scales and offsets of K, then of V
+// (each a multiple of 16 bytes)
+__host__ __device__ __forceinline__ int raw_bytes(const SectionBytes& n)
+{
+    return n.kc + 2 * n.km + n.vc + 2 * n.vm;
+}
+
+template <int D, int KG, bool W8, bool ROT>
+struct FusedLds {  // two images, query fragments, rotation scratch, raw ring
+    static constexpr int kQuery = 2 * image_bytes<D>();
+    static constexpr int kScratch = kQuery + 4 * query_lds_fragments<D, KG>() * 1024;
+    static constexpr int kRaw = kScratch + (ROT ? scratch_bytes<D>() : 0);
+};
+
+template <int D, int KG, bool W8, bool ROT>
+__global__ __launch_bounds__(kFusedThreads, 2) void fused_kernel(AttnParams p)
+{
+    using LD = FusedLds<D, KG, W8, ROT>;
+    constexpr int BI = image_bytes<D>(), NR = raw_slots<D, W8, ROT>();
+    extern __shared__ __attribute__((aligned(16))) uint8_t plds[];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int L = xcd_item(), S = p.S_tot;
+    const int us = __builtin_amdgcn_readfirstlane(L / p.pf_tiles), uloc = __builtin_amdgcn_readfirstlane(us / S);
+    const int split = us - uloc * S;
+    const Tile t = make_tile(p, p.pf_u0 + uloc, p.pf_tiles - 1 - (L - us * p.pf_tiles), kFusedRows);
+    const int it0 = __builtin_amdgcn_readfirstlane((int)((long long)t.nvis * split / S));
+    const int it1 = __builtin_amdgcn_readfirstlane((int)((long long)t.nvis * (split + 1) / S));
+    const auto tail_block = [&](int it) { return it < t.nsb ? it - (p.sink >> 5) : it - t.nsb; };
+    const auto code_at = [&](int it) { return code_block<D>(p, it < t.nsb, tail_block(it)); };
+    // Barriers, the same number for every wave: the first packed block has
+    // landed; the first image is built; then one per block.
+    if (wave < 4) {
+        auto sync = [&]() {
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        Wave<D, KG, 1> w;
+        w.init(p, t, plds + LD::kQuery, wave, lane);
+        sync();
+        sync();
+        for (int it = it0; it < it1; ++it) {
+            const uint8_t* img = plds + ((it - it0) & 1) * BI;
+            w.scores(img, code_at(it), lane, [](int) {});
+            w.update(img, tail_block(it), lane);
+            sync();
+        }
+        w.finish(p, t, split, wave, lane);
+        return;
+    }
+
+    // ---- waves 4 .. 7: packed blocks and images
+    const int bw = wave - 4;
+    const SectionBytes n = section_bytes<D, W8>(p);
+    const int rs = raw_bytes(n), ncb = (p.nq + 31) >> 5;  // ncb: blocks of coded tokens
+    const Sections g = cache_sections(p, n, (size_t)t.unit * (p.T >> 5));
+    const uint32_t lbase = (uint32_t)(uintptr_t)plds + LD::kRaw;
+    // wave 0 copies the K codes, 1 the K scales and offsets, 2 and 3 those of
+    // V, 1 KiB at a time
+    const bool val = bw >= 2, codes = (bw & 1) == 0;
+    const int clen = val ? n.vc : n.kc, mlen = val ? n.vm : n.km, at0 = (val ? n.kc + 2 * n.km : 0) + (codes ? 0 : clen);
+    const uint8_t* src0 = codes ? (val ? g.vc : g.kc) : (val ? g.vs : g.ks);
+    const uint8_t* src1 = codes ? nullptr : (val ? g.vz : g.kz);
+    const int len = codes ? clen : mlen;
+    const int cw = ncb > 0 ? ((len + 1023) >> 10) * (src1 ? 2 : 1) : 0;  // this wave's copies of a block
+    // copies of block `it` (clamped to the coded blocks; a block of fp16 rows is
+    // read from the cache when its image is built)
+    auto copy_raw = [&](int it, int slot) __attribute__((always_inline)) {
+        if (ncb == 0)
+            return;
+        const int blk = min(max(it - t.nsb, 0), ncb - 1);
+        for (int o = 0; o < len; o += 1024)
+            if (o + 16 * lane < len) {
+                const size_t off = (size_t)blk * len + o;
+                copy16((uint64_t)(src0 + off), 16 * lane, lbase + (uint32_t)(slot * rs + at0 + o));
+                if (src1)
+                    copy16((uint64_t)(src1 + off), 16 * lane, lbase + (uint32_t)(slot * rs + at0 + mlen + o));
+            }
+    };
+    auto build = [&](int it, int slot, int im) __attribute__((always_inline)) {
+        const int blk = tail_block(it);
+        const bool sinkblk = it < t.nsb;
+        uint8_t* img = plds + im * BI;
+        float* scratch = (float*)(plds + LD::kScratch);
+        const int tid = threadIdx.x - 256;
+        if (!sinkblk && blk < ncb) {
+            const uint8_t* r = plds + LD::kRaw + slot * rs;
+            Sections s;
+            s.kc = r;
+            s.ks = r + n.kc;
+            s.kz = s.ks + n.km;
+            s.vc = s.kz + n.km;
+            s.vs = s.vc + n.vc;
+            s.vz = s.vs + n.vm;
+            coded_image<D, W8, (KG > 0), ROT>(p, s, min(32, p.nq - 32 * blk), img, scratch, tid);
+        } else {
+            rows_image<D, ROT>(p, t.unit, sinkblk ? it : -1, blk, img, scratch, tid);
+        }
+    };
+    // this wave's LDS writes are done, its copies but the newest `after` have
+    // landed, and all waves are past the same point
+    auto sync = [&](int after) {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+        ring_sync(after);
+    };
+    uint32_t m0_saved;
+    asm volatile("s_mov_b32 %0, m0" : "=s"(m0_saved));
+    if (it0 < it1)
+        for (int j = 0; j < NR; ++j)
+            copy_raw(it0 + j, j);
+    sync(cw * (NR - 1));
+    if (it0 < it1)
+        build(it0, 0, 0);
+    sync(cw * (NR - 2));
+    int slot = 0;  // raw slot of block `it`
+    for (int it = it0; it < it1; ++it) {
+        copy_raw(it + NR, slot);  // block it's image is built: its slot is free
+        slot = slot + 1 == NR ? 0 : slot + 1;
+        if (it + 1 < it1)
+            build(it + 1, slot, (it + 1 - it0) & 1);
+        sync(cw * (NR - 2));
+    }
+    asm volatile("s_mov_b32 m0, %0" ::"s"(m0_saved));
+    __builtin_amdgcn_s_waitcnt(0);  // the trailing copies have landed before the LDS is given back
+}
+
+// O = sum_s 2^(m_s - M) o_s / sum_s 2^(m_s - M) l_s over the key ranges of a
+// query row, four channels per thread.
+constexpr int kMergeThreads = 256;
+
+template <int D>
+__global__ __launch_bounds__(kMergeThreads) void merge_kernel(AttnParams p)
+{
+    const int rows = p.C * p.G, S = p.S_tot;
+    const int R = blockIdx.x * (kMergeThreads / (D / 4)) + threadIdx.x / (D / 4), d = 4 * (threadIdx.x % (D / 4));
+    if (R >= rows)
+        return;
+    const int uloc = blockIdx.y, unit = p.pf_u0 + uloc;
+    const float* ml = p.part_ml + 2 * ((size_t)uloc * S * rows + R);
+    const float* po = p.part_o + ((size_t)uloc * (S - 1) * rows + R) * D + d;
+    const int i = R / p.G, g = R % p.G;
+    // the first range's partial is where the output goes
+    float* dst = p.out + (((size_t)(unit / p.H) * p.C + i) * p.H_q + (size_t)(unit % p.H) * p.G + g) * D + d;
+    float M = -INFINITY;
+    for (int s = 0; s < S; ++s)
+        M = fmaxf(M, ml[2 * (size_t)s * rows]);
+    auto weight = [&](float m) { return m == -INFINITY ? 0.0f : fast_exp2(m - M); };
+    float w0 = weight(ml[0]), l = ml[1] * w0;
+    floatx4 acc = *(const floatx4*)dst * w0;
+#pragma unroll 4
+    for (int s = 1; s < S; ++s) {
+        const float2 v = *(const float2*)(ml + 2 * (size_t)s * rows);
+        const float w = weight(v.x);
+        acc += *(const floatx4*)(po + (size_t)(s - 1) * rows * D) * w;
+        l += v.y * w;
+    }
+    *(floatx4*)dst = acc * (l > 0.0f ? 1.0f / l : 0.0f);
+}
+
+typedef void (*Kernel)(AttnParams);
+
+template <int D>
+Kernel pick(int kg)
+{
+    constexpr int NW = waves<D>();
+    return kg == 1   ? attn_kernel<D, (D >= 256 ? 0 : 1), NW>
+           : kg == 2 ? attn_kernel<D, 2, NW>
+           : kg == 4 ? attn_kernel<D, (D >= 128 ? 4 : 1), NW>
+           : kg == 8 ? attn_kernel<D, (D >= 256 ? 8 : 1), NW>
+                     : attn_kernel<D, 0, NW>;
+}
+
+// Key ranges per query tile on the fused path, or 0 for the workspace path.
+// The choice and the count depend on the call alone, not on the workspace
+// given, so that a smaller workspace changes no output bit.  The estimates are
+// of the whole call, from times per 32-token block measured at contexts of
+// 1000 to 8192 tokens and chunks of 32 to 2048: building an image (chip-wide),
+// a block's products for one round of workgroups (256 rows), and a block of
+// the fused path (128 rows; reconstruction is its limit, and a rotating
+// format's costs two to three times as much).  Measured at B = 1, C = 32 of
+// 8192 tokens: 30 to 70 us fused against 220 to 470; at B = 8, C = 200 of 3000
+// and D = 128: 250 against 152.
+template <int D>
+int fused_splits(const AttnParams& p)
+{
+    if (D == 256 && p.rotate && p.k_bits == 8)
+        return 0;  // two images, the scratch and two packed blocks exceed the LDS
+    const long long units = (long long)p.B * p.H, rows = (long long)p.C * p.G, nb = p.pf_nvb;
+    const double dq = D == 64 ? 0.004 : D == 128 ? 0.007 : 0.0106, a = D == 64 ? 1.0 : D == 128 ? 1.15 : 1.9;  // us
+    const double f = p.rotate ? (D == 64 ? 1.7 : D == 128 ? 3.1 : 5.7) : (D == 64 ? 1.0 : D == 128 ? 1.3 : 2.2);
+    const auto rounds = [](long long wgs, int at_once) { return (double)((wgs + at_once - 1) / at_once); };
+    const double image = units * nb * dq + nb * a * rounds(units * ((rows + kRows - 1) / kRows), D == 64 ? 512 : 256);
+    // Key ranges: to fill the CUs, at least four blocks each, and their
+    // partials (the first range's outputs wait in O itself) within the units'
+    // shares of the workspace
+    const long long wgs = units * ((rows + kFusedRows - 1) / kFusedRows);
+    long long S = 256 / wgs < nb / 4 ? 256 / wgs : nb / 4;
+    while (S > 1 && (S - 1) * rows * D * 4 + S * rows * 8 > nb * image_bytes<D>())
+        --S;
+    S = S < 1 ? 1 : S;
+    const double fused = (S > 1 ? 10.0 : 0.0) + (double)((nb + S - 1) / S) * f * rounds(wgs * S, 256);
+    return fused < image ? (int)S : 0;
+}
+
+template <int D, int KG, bool W8, bool ROT>
+void launch_fused(const AttnParams& p, int groups, hipStream_t stream)
+{
+    const size_t lds = FusedLds<D, KG, W8, ROT>::kRaw + (size_t)raw_slots<D, W8, ROT>() * raw_bytes(section_bytes<D, W8>(p));
+    launch_kernel(fused_kernel<D, KG, W8, ROT>, dim3(groups), dim3(kFusedThreads), lds, stream, p);
+}
+
+template <int D, bool W8>
+void launch_fused(const AttnParams& p, int kg, int groups, hipStream_t stream)
+{
+    if (p.rotate) {
+        if constexpr (!(D == 256 && W8))
+            launch_fused<D, 0, W8, true>(p, groups, stream);
+    } else if (kg == 1 && D < 256) {
+        launch_fused<D, D < 256 ? 1 : 0, W8, false>(p, groups, stream);
+    } else if (kg == 2) {
+        launch_fused<D, 2, W8, false>(p, groups, stream);
+    } else if (kg == 4) {
+        launch_fused<D, D >= 128 ? 4 : 2, W8, false>(p, groups, stream);
+    } else if (kg == 8) {
+        launch_fused<D, D >= 256 ? 8 : 2, W8, false>(p, groups, stream);
+    } else {
+        launch_fused<D, 0, W8, false>(p, groups, stream);
+    }
 }
 
 template <int D>
@@ -1007,15 +1465,49 @@ hipError_t launch(const AttnParams& p0, size_t ws_bytes, hipStream_t stream)
     const int group = (int)(ws_bytes / per_unit < (size_t)units ? ws_bytes / per_unit : (size_t)units);
     if (group < 1)
         return hipErrorInvalidValue;
-    const int tiles = (p0.C * p0.G + kRows - 1) / kRows;
+    const int rows = p0.C * p0.G;
     const bool w8 = p0.k_bits == 8;  // 8-bit codes come as K and V both 8-bit
-    void (*deq)(AttnParams) = w8 ? (rot ? dequant_kernel<D, true, true> : dequant_kernel<D, true, false>)
-                                 : (rot ? dequant_kernel<D, false, true> : dequant_kernel<D, false, false>);
     // per-token key groups of 32 KG channels (a power of two from 32 to D)
     const int kg = p0.k_axis == KVQ_PER_TOKEN ? p0.k_group / 32 : 0;
     if (kg != 0 && kg != 1 && kg != 2 && !(kg == 4 && D >= 128) && !(kg == 8 && D >= 256))
         return hipErrorInvalidValue;
-    void (*att)(AttnParams) = pick<D>(rot ? 0 : kg);
+    const int splits = fused_splits<D>(p0);
+    if (splits > 0) {
+        constexpr int MR = kMergeThreads / (D / 4);  // rows per merge workgroup
+        for (int u0 = 0; u0 < units; u0 += group) {
+            AttnParams p = p0;
+            p.pf_u0 = u0;
+            p.pf_tiles = (rows + kFusedRows - 1) / kFusedRows;
+            p.S_tot = splits;
+            const int nu = units - u0 < group ? units - u0 : group;
+            p.part_o = (float*)p.pf_ws;
+            p.part_ml = p.part_o + (size_t)nu * (splits - 1) * rows * D;
+            const int groups = p.pf_tiles * splits * nu;
+            if (w8)
+                launch_fused<D, true>(p, kg, groups, stream);
+            else
+                launch_fused<D, false>(p, kg, groups, stream);
+            if (splits > 1)
+                launch_kernel(merge_kernel<D>, dim3((rows + MR - 1) / MR, nu), dim3(kMergeThreads), 0, stream, p);
+        }
+        return hipGetLastError();
+    }
+    void (*deq)(AttnParams) = w8 ? (rot ? dequant_kernel<D, true, true> : dequant_kernel<D, true, false>)
+                                 : (rot ? dequant_kernel<D, false, true> : dequant_kernel<D, false, false>);
+    Kernel att = pick<D>(rot ? 0 : kg);
+    int nw = waves<D>(), per = kRows;
+    if constexpr (D == 256) {
+        // hi + lo keys at D = 256 are bound by LDS reads (48 KiB per wave and
+        // block), which half the waves halve: where tiles of 256 rows do not
+        // cover the CUs, four waves of 128 rows (measured at 64 such tiles:
+        // 265 -> 232 us; with code blocks no gain)
+        if ((rot || kg <= 1) && units * ((rows + kRows - 1) / kRows) <= 128) {
+            att = attn_kernel<D, 0, 4>;
+            nw = 4;
+            per = 128;
+        }
+    }
+    const int tiles = (rows + per - 1) / per;
     for (int u0 = 0; u0 < units; u0 += group) {
         AttnParams p = p0;
         p.pf_u0 = u0;
@@ -1023,12 +1515,24 @@ hipError_t launch(const AttnParams& p0, size_t ws_bytes, hipStream_t stream)
         p.S_tot = 1;
         const int nu = units - u0 < group ? units - u0 : group;
         launch_kernel(deq, dim3(p.pf_nvb, nu), dim3(kDqThreads), rot ? scratch_bytes<D>() : 0, stream, p);
-        launch_kernel(att, dim3(tiles * nu), dim3(threads<D>()), attn_lds_bytes<D>(), stream, p);
+        launch_kernel(att, dim3(tiles * nu), dim3(64 * nw), attn_lds_bytes<D>(), stream, p);
     }
     return hipGetLastError();
 }
 
 }  // namespace pre
+
+// Built once per head size (KVQ_PREFILL_D): the kernels of one size take as
+// long to compile as the rest of the library.
+hipError_t launch_prefill_64(const AttnParams& p, size_t ws_bytes, hipStream_t stream);
+hipError_t launch_prefill_128(const AttnParams& p, size_t ws_bytes, hipStream_t stream);
+hipError_t launch_prefill_256(const AttnParams& p, size_t ws_bytes, hipStream_t stream);
+
+#if KVQ_PREFILL_D == 64
+hipError_t launch_prefill_64(const AttnParams& p, size_t ws_bytes, hipStream_t stream)
+{
+    return pre::launch<64>(p, ws_bytes, stream);
+}
 
 size_t prefill_image_bytes(int D)
 {
@@ -1039,14 +1543,25 @@ hipError_t launch_prefill(const AttnParams& p, int D, size_t ws_bytes, hipStream
 {
     switch (D) {
     case 64:
-        return pre::launch<64>(p, ws_bytes, stream);
+        return launch_prefill_64(p, ws_bytes, stream);
     case 128:
-        return pre::launch<128>(p, ws_bytes, stream);
+        return launch_prefill_128(p, ws_bytes, stream);
     case 256:
-        return pre::launch<256>(p, ws_bytes, stream);
+        return launch_prefill_256(p, ws_bytes, stream);
     default:
         return hipErrorInvalidValue;
     }
 }
+#elif KVQ_PREFILL_D == 128
+hipError_t launch_prefill_128(const AttnParams& p, size_t ws_bytes, hipStream_t stream)
+{
+    return pre::launch<128>(p, ws_bytes, stream);
+}
+#else
+hipError_t launch_prefill_256(const AttnParams& p, size_t ws_bytes, hipStream_t stream)
+{
+    return pre::launch<256>(p, ws_bytes, stream);
+}
+#endif
 
 }  // namespace kvq

@@ -1,0 +1,50 @@
+"""Both ways of the chunked prefill attention, at the edges of their tiles and splits.
+
+Few query rows take the fused path (packed blocks reconstructed in LDS, the
+key range split over workgroups when there are few query tiles), many rows the
+workspace path (block images, 256-row tiles; 128 at D = 256 for hi + lo keys
+and few tiles).  Each case is checked against the fp64 oracle as in
+test_gpu_prefill (2e-3 + 1e-2 |ref|), with lengths that leave a partial last
+block, rows that leave a partial last tile, fp16 windows and sinks, rotation,
+every code width and mixed widths.
+"""
+import numpy as np
+import pytest
+
+from test_gpu_prefill import run
+
+pytestmark = pytest.mark.gpu
+
+NAMES = ["tiny_b16", "affine8", "sink64", "sym4_window", "kivi", "kivi_meta16", "hadamard", "perch_k4v2_window64",
+         "kvarn_sink", "perch8_meta16", "gqa12b", "g256", "had_affine_window", "sym8_window_d256"]
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_fused_key_ranges(name):
+    # 1 unit, 46 rows, 47 blocks: one tile and eleven key ranges, the last block partial
+    run(name, B=1, H=1, G=2, n=1493, C=23, seed=410)
+
+
+@pytest.mark.parametrize("name", ["tiny_b16", "kivi", "gqa12b"])
+@pytest.mark.parametrize("C", [31, 32, 33, 64, 65])
+def test_fused_tile_edges(name, C):
+    # 4 C rows: 124 .. 260 on tiles of 128
+    run(name, B=1, H=2, G=4, n=400 + C, C=C, seed=420 + C)
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_workspace_tiles(name):
+    # 32 units of 1 + 4 tiles of 256 rows: the workspace path at every head size
+    run(name, B=4, H=8, G=4, n=293, C=260, seed=430)
+
+
+@pytest.mark.parametrize("name", ["had_affine_window", "gqa12b"])
+def test_workspace_few_tiles_d256(name):
+    run(name, B=2, H=8, G=4, n=293, C=260, seed=440)
+
+
+@pytest.mark.parametrize("name", ["tiny_b16", "kivi", "gqa12b", "hadamard"])
+def test_split_outputs_do_not_depend_on_the_workspace(name):
+    # 6 units in one pass, in groups of 4 + 2, and one at a time
+    outs = [run(name, B=3, H=2, G=2, n=1100, C=30, seed=450, ws_units=u) for u in (None, 4, 1)]
+    assert np.array_equal(outs[0], outs[1]) and np.array_equal(outs[0], outs[2])
