@@ -10,7 +10,7 @@
 // M <= 32 (decode: one token per sequence) streams the weights from HBM
 // with whole-line loads staged through LDS; its activation pass is split
 // over K (see the decode section).  Larger M (prefill) uses a 256x256 tiled
-// GEMM staged through LDS, or a 128x128 one for small shapes.
+// GEMM staged through LDS, or smaller tiles where those leave the chip idle.
 
 #include <atomic>
 
@@ -1375,6 +1375,298 @@ __global__ __launch_bounds__(kPThreads, 1) void proj_gemm_pp_kernel(ProjParams p
     }
 }
 
+// -------------------------------------------------------------------- mid
+// M from 33 to about 2000 rows: tiles of 32 MI WM x 32 NI WN, one of a few
+// sizes chosen so that the tiles cover the compute units (mid_tile), WM x WN
+// waves of 32 MI x 32 NI each.  256x256 tiles leave most of the chip idle there
+// (48 workgroups at M = 333, N = 6144: 75 us of which each CU reads 4 MiB), and
+// a tile's time is bound by the LDS reads of its fragments and by the 100 to
+// 140 GB/s at which one CU reads from L2, both of which favour tiles that are
+// not too thin.  Operands reach LDS by global_load_lds_dwordx4 in a ring of NST
+// stages of K = 64: copies of 8 rows x 128 bytes (whole lines), chunk c of row
+// r at chunk position c ^ gemm_swz(r).  One barrier per stage; copies NST - 1
+// stages ahead.  Every output is the same chain of v_mfma_f32_32x32x16_bf16
+// over K, then over the adapter's hi and lo parts, as in proj_gemm_kernel and
+// proj_gemm_pp_kernel, so its bits do not depend on which of them computes it
+// (the fused append relies on that).  Tiles that share weight columns run on
+// one XCD, so that the weights are read from HBM once.
+// Projection of 333 rows, d_in 4096, 6144 outputs, rank 16: 111 us (activation
+// 38.6, main 75) -> 41 to 43; 100 rows 103 -> 28.
+template <int MI, int NI, int WM, int WN, int NST>
+struct MidShape {
+    static constexpr int BM = 32 * MI * WM, BN = 32 * NI * WN, NW = WM * WN;
+    static constexpr int STAGE = (BM + BN) * 128;
+    static constexpr int CPW = (BM + BN) / 8 / NW;  // copies per wave and stage
+    static_assert((BM + BN) / 8 % NW == 0 && BM % 8 == 0, "whole copies per wave");
+    static constexpr size_t LDS = (size_t)NST * STAGE;
+};
+
+template <int MI, int NI, int WM, int WN, int NST>
+__global__ __launch_bounds__(64 * WM * WN, 1) void proj_mid_kernel(ProjParams p)
+{
+    using S = MidShape<MI, NI, WM, WN, NST>;
+    constexpr int BM = S::BM, BN = S::BN, CPW = S::CPW;
+    extern __shared__ __attribute__((aligned(16))) uint8_t glds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+    const int nbm = (p.M + BM - 1) / BM, nbn = (p.N + BN - 1) / BN, ntiles = nbm * nbn;
+    // XCD x (= workgroup id mod p.nxcd) takes the contiguous range of tiles
+    // [x per, (x + 1) per), row blocks fastest
+    const int per = (ntiles + p.nxcd - 1) / p.nxcd;
+    const int t = (blockIdx.x % p.nxcd) * per + blockIdx.x / p.nxcd;
+    if (t >= ntiles)
+        return;
+    const int m0 = t % nbm * BM, n0 = t / nbm * BN;
+
+    // copy c of this wave: rows 8 j .. 8 j + 7 of the stage (A rows, then B
+    // rows), j = CPW wave + c; lane i writes row 8 j + i / 8, chunk position i %
+    // 8, which holds source chunk (i % 8) ^ swz(row).  Rows past M (N) re-read
+    // the last row; their results are never stored.
+    uint64_t base[CPW];
+    uint32_t voff[CPW];
+#pragma unroll
+    for (int c = 0; c < CPW; ++c) {
+        const int j = CPW * wave + c, row = 8 * j + (lane >> 3);
+        const bool isb = 8 * j >= BM;
+        const int r = isb ? row - BM : row, last = isb ? p.N - 1 - n0 : p.M - 1 - m0;
+        base[c] = isb ? (uint64_t)(p.w + (size_t)n0 * p.K) : (uint64_t)(p.x + (size_t)m0 * p.K);
+        voff[c] = (uint32_t)min(r, last) * (uint32_t)p.K * 2u + 16u * (uint32_t)((lane & 7) ^ gemm_swz(row));
+    }
+    const uint32_t lbase = (uint32_t)(uintptr_t)glds;
+    const int nks = p.K / 64;
+    // (stages past the end re-load the last one into a slot that is not read again)
+    auto copy_stage = [&](int ks, int slot) {
+        const uint64_t ko = (uint64_t)min(ks, nks - 1) * 128;
+#pragma unroll
+        for (int c = 0; c < CPW; ++c) {
+            const uint64_t b = base[c] + ko;
+            const uint32_t bl = __builtin_amdgcn_readfirstlane((uint32_t)b);
+            const uint32_t bh = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+            pp_copy16(((uint64_t)bh << 32) | bl, voff[c], lbase + slot * S::STAGE + (CPW * wave + c) * 1024);
+        }
+    };
+    // stage ks + 1 has landed (this wave's copies but those of the newest NST -
+    // 2 stages), and every wave is past stage ks
+    auto sync = [&]() {
+        constexpr int vm = CPW * (NST - 2);
+        static_assert(vm < 64, "vmcnt");
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0x0F70 | (vm & 15) | ((vm >> 4) << 14));
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    const int fr = lane & 31, fk = lane >> 5;
+    int aoff[4], boff[4];  // chunk 2 kt + fk of the lane's row
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt) {
+        const int ra = 32 * MI * wm + fr, rb = BM + 32 * NI * wn + fr;
+        aoff[kt] = ra * 128 + 16 * ((2 * kt + fk) ^ gemm_swz(ra));
+        boff[kt] = rb * 128 + 16 * ((2 * kt + fk) ^ gemm_swz(rb));
+    }
+    floatx16 acc[MI][NI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+            acc[i][j] = floatx16{};
+
+    uint32_t m0_saved;
+    asm volatile("s_mov_b32 %0, m0" : "=s"(m0_saved));
+#pragma unroll
+    for (int ks = 0; ks < NST - 1; ++ks)
+        copy_stage(ks, ks);
+    sync();
+    int slot = 0;
+    for (int ks = 0; ks < nks; ++ks) {
+        copy_stage(ks + NST - 1, slot == 0 ? NST - 1 : slot - 1);
+        const uint8_t* stg = glds + slot * S::STAGE;
+        bf16x8 fa[4][MI], fb[4][NI];
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt) {
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+                fa[kt][i] = __builtin_bit_cast(bf16x8, *(const u32x4*)(stg + aoff[kt] + 4096 * i));
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+                fb[kt][j] = __builtin_bit_cast(bf16x8, *(const u32x4*)(stg + boff[kt] + 4096 * j));
+        }
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+                    acc[i][j] = mfma32_bf16(fa[kt][i], fb[kt][j], acc[i][j]);
+        slot = slot + 1 == NST ? 0 : slot + 1;
+        sync();
+    }
+    asm volatile("s_mov_b32 m0, %0" ::"s"(m0_saved));
+    __builtin_amdgcn_s_waitcnt(0);  // the trailing copies have landed before the LDS is given back
+
+    // adapter branch: K-extension over the rank, 16 at a time (hi, then lo)
+    if (p.rank > 0) {
+        const bool vec = (p.rank & 15) == 0;
+        const int p_lo = proj_of(p, n0), p_hi = proj_of(p, min(n0 + BN, p.N) - 1);
+        for (int proj = p_lo; proj <= p_hi; ++proj) {
+            for (int k0 = 0; k0 < p.rank; k0 += 16) {
+                const int k = k0 + 8 * fk;
+                bf16x8 wop[NI], hi[MI], lo[MI];
+#pragma unroll
+                for (int j = 0; j < NI; ++j) {
+                    const int n = n0 + 32 * (NI * wn + j) + fr;
+                    const bool ok = n < p.N && proj_of(p, n) == proj;
+                    const uint16_t* src = p.bm + (size_t)min(n, p.N - 1) * p.rank;
+                    if (vec) {
+                        const bf16x8 w = load_bf16x8(src + k);
+                        wop[j] = ok ? w : zero_bf16x8();
+                    } else {
+                        uint16_t v[8];
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            v[e] = ok && k + e < p.rank ? src[k + e] : (uint16_t)0;
+                        wop[j] = __builtin_bit_cast(bf16x8, u32x4{v[0] | ((uint32_t)v[1] << 16), v[2] | ((uint32_t)v[3] << 16),
+                                                                  v[4] | ((uint32_t)v[5] << 16), v[6] | ((uint32_t)v[7] << 16)});
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < MI; ++i) {
+                    const int m = m0 + 32 * (MI * wm + i) + fr;
+                    const float* src = p.t + (size_t)min(m, p.M - 1) * 3 * p.rank + proj * p.rank;
+                    float v[8];
+                    if (vec) {
+                        const float4 a = *(const float4*)(src + k), b = *(const float4*)(src + k + 4);
+                        const float w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            v[e] = m < p.M ? w[e] : 0.0f;
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            v[e] = m < p.M && k + e < p.rank ? src[k + e] : 0.0f;
+                    }
+                    split_bf16x8(v, &hi[i], &lo[i]);
+                }
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+#pragma unroll
+                    for (int j = 0; j < NI; ++j) {
+                        acc[i][j] = mfma32_bf16(hi[i], wop[j], acc[i][j]);
+                        acc[i][j] = mfma32_bf16(lo[i], wop[j], acc[i][j]);
+                    }
+            }
+        }
+    }
+    // element e of lane l: row 8 (e / 4) + 4 (l / 32) + e % 4, column l % 32 of its block
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+        const int n = n0 + 32 * (NI * wn + j) + fr;
+        if (n >= p.N)
+            continue;
+        const int proj = proj_of(p, n);
+        uint16_t* y = proj == 0 ? p.y0 : proj == 1 ? p.y1 : p.y2;
+        const int width = proj == 0 ? p.n1 : proj == 1 ? p.n2 - p.n1 : p.N - p.n2;
+        const int col = n - (proj == 0 ? 0 : proj == 1 ? p.n1 : p.n2);
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int m = m0 + 32 * (MI * wm + i) + 8 * (e >> 2) + 4 * fk + (e & 3);
+                if (m < p.M)
+                    y[(size_t)m * width + col] = f32_to_bf16(acc[i][j][e]);
+            }
+    }
+}
+
+// Activation pass: workgroup (16 MT tokens, 16 NT adapter rows), eight waves
+// over the 64-wide steps of K, their sums added in LDS (a tree, so that at most
+// half of the waves' accumulators are there at once).  A lane reads 32
+// contiguous bytes of its row per step (whole lines) and feeds them to two
+// MFMAs: any order of K serves, as long as both operands have the same.  Every
+// workgroup reads all of K of its tokens and of its adapter rows, so short
+// calls take the smallest tiles (more workgroups) and long ones 64 tokens.
+constexpr int kActWaves = 8;
+
+template <int MT, int NT>
+__global__ __launch_bounds__(64 * kActWaves, 2) void proj_act_kernel(ProjParams p)
+{
+    __shared__ floatx4 red[kActWaves / 2][MT * NT][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r = lane & 15, qg = lane >> 4;
+    const int m0 = 16 * MT * blockIdx.y, n0 = 16 * NT * blockIdx.x;
+    const uint16_t *xp[MT], *wp[NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+        xp[i] = p.x + (size_t)min(m0 + 16 * i + r, p.M - 1) * p.K + 16 * qg;
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+        wp[j] = p.w + (size_t)min(n0 + 16 * j + r, p.N - 1) * p.K + 16 * qg;
+    floatx4 acc[MT][NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+            acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    constexpr int U = MT * NT == 1 ? 4 : 1;  // steps in flight
+    const int steps = p.K / 64;
+    for (int s0 = wave; s0 < steps; s0 += U * kActWaves) {
+        bf16x8 a[U][MT][2], b[U][NT][2];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            // (past the end: the last step again, its products left out)
+            const size_t k = 64 * (size_t)min(s0 + u * kActWaves, steps - 1);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+                    a[u][i][h] = load_bf16x8(xp[i] + k + 8 * h);
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+                    b[u][j][h] = load_bf16x8(wp[j] + k + 8 * h);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (s0 + u * kActWaves < steps) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int i = 0; i < MT; ++i)
+#pragma unroll
+                        for (int j = 0; j < NT; ++j)
+                            acc[i][j] = mfma16_bf16(a[u][i][h], b[u][j][h], acc[i][j]);
+            }
+    }
+    for (int half = kActWaves / 2; half > 0; half >>= 1) {
+        if (wave >= half && wave < 2 * half) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+                    red[wave - half][i * NT + j][lane] = acc[i][j];
+        }
+        __syncthreads();
+        if (wave < half) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+                    acc[i][j] += red[wave][i * NT + j][lane];
+        }
+        __syncthreads();
+    }
+    if (wave > 0)
+        return;
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                store_out(p, m0 + 16 * i + 4 * qg + e, n0 + 16 * j + r, acc[i][j][e]);
+}
+
 // XCDs of the current device (1 when unknown), cached per device.
 int gemm_xcds()
 {
@@ -1390,11 +1682,45 @@ int gemm_xcds()
     return nx;
 }
 
+template <int MI, int NI, int WM, int WN, int NST>
+void launch_mid(const ProjParams& p, hipStream_t stream)
+{
+    using S = MidShape<MI, NI, WM, WN, NST>;
+    const int tiles = ((p.M + S::BM - 1) / S::BM) * ((p.N + S::BN - 1) / S::BN), per = (tiles + p.nxcd - 1) / p.nxcd;
+    launch_kernel((proj_mid_kernel<MI, NI, WM, WN, NST>), dim3(per * p.nxcd), dim3(64 * WM * WN), S::LDS, stream, p);
+}
+
 }  // namespace
+
+// Tile of the mid kernel for a main pass of M x N outputs (0: 128x128, 1:
+// 128x64, 2: 64x64), or -1 for the 256x256 tiles of the large-M kernel.  The
+// estimates (us at K = 4096; all scale with K) are fits to calls of 40 to 3000
+// rows at 2560, 6144 and 8192 outputs: one workgroup per CU for the 128x128
+// tiles (160 KiB ring), two for the smaller ones.  Measured (whole calls, 6144
+// outputs, d_in 4096, rank 16; 128x128 / 128x64 / 64x64 / 256x256): 100 rows
+// 47.7 / 34.6 / 27.6 / -; 333 rows 48.1 / 43.3 / 50.0 / 82.4; 1024 rows 87.9 /
+// 75.2 / 88.9 / 85.3; 1500 rows 142 / 119 / 154 / 95.9.  (128x96 and 64x32 tiles
+// were within 4% of the best of these or slower everywhere.)
+static int mid_tile(int M, int N)
+{
+    const auto tiles = [&](int bm, int bn) { return (double)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+    const double n0 = tiles(128, 128), n1 = tiles(128, 64), n2 = tiles(64, 64), n = tiles(256, 256);
+    const double t[3] = {n0 <= 256 ? 38.0 : 0.19 * n0,
+                         n1 <= 256 ? 24.5 : n1 <= 512 ? 36.0 : n1 <= 667 ? 60.0 : 0.09 * n1,
+                         n2 <= 256 ? 17.5 : n2 <= 512 ? 27.0 : 0.058 * n2};
+    int best = t[1] < t[0] ? 1 : 0;
+    best = t[2] < t[best] ? 2 : best;
+    if (M >= kGM && N >= kGN) {
+        const double full = (double)((long long)n / 256), rest = n - 256 * full;
+        if (100.0 * full + (rest > 0 ? 70.0 + 0.12 * rest : 0.0) <= t[best])
+            return -1;
+    }
+    return best;
+}
 
 bool project_adapter_stages(int M, int d_in, int d_q, int d_kv, int rank)
 {
-    return rank > 0 && rank % 16 == 0 && M >= kGM && d_q + 2 * d_kv >= kGN && d_in % kGK == 0 && d_q % kGN == 0 &&
+    return mid_tile(M, d_q + 2 * d_kv) < 0 && rank > 0 && rank % 16 == 0 && M >= kGM && d_q + 2 * d_kv >= kGN && d_in % kGK == 0 && d_q % kGN == 0 &&
            d_kv % kGN == 0;
 }
 
@@ -1435,8 +1761,23 @@ hipError_t launch_project(const ProjParams& p, hipStream_t stream)
     const bool tiled = p.M >= kGM && p.N >= kGN && !p.yf && p.K % kGK == 0;
     if (p.t_hilo && !p.yf && (!tiled || p.fuse || p.rank % 16 != 0))
         return hipErrorInvalidValue;  // only the large-M pass reads bf16 hi / lo activations
-    if (p.M <= 32 && !p.yf) {
+    if (p.M <= 32 && !p.yf)
         return launch_project_decode(p, stream);
+    const int mid = p.yf || p.fuse || p.K % 64 != 0 ? -1 : mid_tile(p.M, p.N);
+    if (mid >= 0) {
+        ProjParams q = p;
+        q.nxcd = gemm_xcds();
+        switch (mid) {
+        case 0:
+            launch_mid<2, 2, 2, 2, 4>(q, stream);
+            break;
+        case 1:
+            launch_mid<2, 1, 2, 2, 3>(q, stream);
+            break;
+        default:
+            launch_mid<1, 1, 2, 2, 4>(q, stream);
+            break;
+        }
     } else if (tiled) {
         const int tiles = ((p.M + kGM - 1) / kGM) * ((p.N + kGN - 1) / kGN);
         ProjParams q = p;
@@ -1446,6 +1787,15 @@ hipError_t launch_project(const ProjParams& p, hipStream_t stream)
             launch_kernel(proj_gemm_kernel<true>, dim3(per * q.nxcd), dim3(kThreads), kGLds, stream, q);
         else
             launch_kernel(proj_gemm_pp_kernel, dim3(per * q.nxcd), dim3(kPThreads), kPLds, stream, q);
+    } else if (p.yf && p.K % 64 == 0 && (long long)((p.M + 15) / 16) * ((p.N + 15) / 16) <= 1536) {
+        // (beyond, the adapter rows each workgroup reads again cost more than
+        // the register-staged tiles below: 4096 rows at rank 64 303 against 268
+        // us a call, 333 rows at rank 16 82 against 112)
+        launch_kernel((proj_act_kernel<1, 1>), dim3((p.N + 15) / 16, (p.M + 15) / 16), dim3(64 * kActWaves), 0, stream, p);
+    } else if (p.yf && p.K % 64 == 0 && (long long)((p.M + 63) / 64) * ((p.N + 47) / 48) <= 256) {
+        // one round of 64 x 48 tiles: 8192 rows at rank 32 501 -> 484 us a call;
+        // with two rounds no gain or slower (12000 rows at rank 64 621 -> 647)
+        launch_kernel((proj_act_kernel<4, 3>), dim3((p.N + 47) / 48, (p.M + 63) / 64), dim3(64 * kActWaves), 0, stream, p);
     } else if (p.yf && p.N <= 2 * kBN && p.M < 256 * kBM) {
         // activation pass with fewer than 256 row tiles of 128: 32-row tiles
         // (every workgroup also reads all of A, so more tiles only pay
