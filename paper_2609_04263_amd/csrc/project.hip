@@ -1707,7 +1707,7 @@ static int mid_tile(int M, int N)
     const double n0 = tiles(128, 128), n1 = tiles(128, 64), n2 = tiles(64, 64), n = tiles(256, 256);
     const double t[3] = {n0 <= 256 ? 38.0 : 0.19 * n0,
                          n1 <= 256 ? 24.5 : n1 <= 512 ? 36.0 : n1 <= 667 ? 60.0 : 0.09 * n1,
-                         n2 <= 256 ? 17.5 : n2 <= 512 ? 27.0 : 0.058 * n2};
+                         n2 <= 256 ? 17.5 : n2 <= 512 ? 27.0 : n2 <= 690 ? 40.0 : 0.058 * n2};
     int best = t[1] < t[0] ? 1 : 0;
     best = t[2] < t[best] ? 2 : best;
     if (M >= kGM && N >= kGN) {
