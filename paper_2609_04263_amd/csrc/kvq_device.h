@@ -65,32 +65,6 @@ __device__ __forceinline__ half8 pack_half8(const float* v)
     return h;
 }
 
-// fp32 -> fp16 hi + lo with hi + lo = v to about 22 significant bits, so an
-// MFMA pair over (hi, lo) carries nearly fp32 precision.
-__device__ __forceinline__ void split_half8(const float* v, half8* hi, half8* lo)
-{
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        _Float16 h = (_Float16)v[e];
-        (*hi)[e] = h;
-        (*lo)[e] = (_Float16)(v[e] - (float)h);
-    }
-}
-
-__device__ __forceinline__ float xor_sum16_32(float v)
-{
-    v += __shfl_xor(v, 16);
-    v += __shfl_xor(v, 32);
-    return v;
-}
-
-__device__ __forceinline__ float xor_max16_32(float v)
-{
-    v = fmaxf(v, __shfl_xor(v, 16));
-    v = fmaxf(v, __shfl_xor(v, 32));
-    return v;
-}
-
 __device__ __forceinline__ float fast_exp2(float x)
 {
     return __builtin_amdgcn_exp2f(x);

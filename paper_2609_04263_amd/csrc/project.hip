@@ -92,21 +92,8 @@ __device__ __forceinline__ void store_out(const ProjParams& p, int m, int n, flo
         p.y2[(size_t)m * (p.N - p.n2) + (n - p.n2)] = o;
 }
 
-// Adapter operands for one 32-wide chunk kk of the rank dimension:
-//   rows side: token m's activations t[m][p r + k] (fp32 -> bf16 hi/lo),
-//   cols side: weight row n's up-projection B[n][k], zero unless n is in p.
-__device__ __forceinline__ void lora_token_operand(const ProjParams& p, int m, int proj, int kk, int qg,
-                                                   bf16x8* hi, bf16x8* lo)
-{
-    float v[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        int k = 32 * kk + 8 * qg + e;
-        v[e] = (m < p.M && k < p.rank) ? p.t[(size_t)m * 3 * p.rank + proj * p.rank + k] : 0.0f;
-    }
-    split_bf16x8(v, hi, lo);
-}
-
+// Adapter operand of weight row n for the 32-wide chunk kk of the rank
+// dimension: the up-projection B[n][k], zero unless n belongs to proj.
 __device__ __forceinline__ bf16x8 lora_weight_operand(const ProjParams& p, int n, int proj, int kk, int qg)
 {
     const bool ok = n < p.N && proj_of(p, n) == proj;
@@ -594,10 +581,11 @@ hipError_t launch_stream_fa(const ProjParams& p, int G, hipStream_t stream)
 }
 
 // --------------------------------------------------------------------- big
+// Activation pass t = H A^T of calls too long for proj_act_kernel's rule:
 // (32 MI)x128 output tile, four waves in a 2x2 grid of (16 MI)x64 sub-tiles,
 // K step 64 through double-buffered LDS (rows padded by 16 bytes).  MI = 4
-// (128-row tiles), or MI = 1 for an activation pass (N = 3 r <= 192
-// columns) too short to cover the compute units with 128-row tiles.
+// (128-row tiles), or MI = 1 for a pass (N = 3 r <= 192 columns) too short to
+// cover the compute units with 128-row tiles.
 // MFMA roles: A = H rows (M-dim = tokens), B = W^T (N-dim = weight rows).
 // Output lane layout: token m = row base + 4 qg + i, column n = base + lane % 16.
 constexpr int kBM = 128, kBN = 128, kBK = 64, kLdsRow = kBK + 8;
@@ -676,28 +664,6 @@ __global__ __launch_bounds__(kThreads) void proj_big_kernel(ProjParams p)
         }
     }
 
-    if (p.rank > 0) {
-        const int nk = (p.rank + 31) / 32;
-        const int p_lo = proj_of(p, n0), p_hi = proj_of(p, min(n0 + kBN, p.N) - 1);
-        for (int proj = p_lo; proj <= p_hi; ++proj) {
-            for (int kk = 0; kk < nk; ++kk) {
-                bf16x8 wop[4];
-#pragma unroll
-                for (int ni = 0; ni < 4; ++ni)
-                    wop[ni] = lora_weight_operand(p, n0 + wn * 64 + 16 * ni + r, proj, kk, qg);
-#pragma unroll
-                for (int mi = 0; mi < MI; ++mi) {
-                    bf16x8 hi, lo;
-                    lora_token_operand(p, m0 + wm * 16 * MI + 16 * mi + r, proj, kk, qg, &hi, &lo);
-#pragma unroll
-                    for (int ni = 0; ni < 4; ++ni) {
-                        acc[mi][ni] = mfma16_bf16(hi, wop[ni], acc[mi][ni]);
-                        acc[mi][ni] = mfma16_bf16(lo, wop[ni], acc[mi][ni]);
-                    }
-                }
-            }
-        }
-    }
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
@@ -1787,16 +1753,18 @@ hipError_t launch_project(const ProjParams& p, hipStream_t stream)
             launch_kernel(proj_gemm_kernel<true>, dim3(per * q.nxcd), dim3(kThreads), kGLds, stream, q);
         else
             launch_kernel(proj_gemm_pp_kernel, dim3(per * q.nxcd), dim3(kPThreads), kPLds, stream, q);
-    } else if (p.yf && p.K % 64 == 0 && (long long)((p.M + 15) / 16) * ((p.N + 15) / 16) <= 1536) {
+    } else if (!p.yf) {
+        return hipErrorInvalidValue;  // a main pass always takes one of the kernels above: d_in is a multiple of 64
+    } else if ((long long)((p.M + 15) / 16) * ((p.N + 15) / 16) <= 1536) {
         // (beyond, the adapter rows each workgroup reads again cost more than
         // the register-staged tiles below: 4096 rows at rank 64 303 against 268
         // us a call, 333 rows at rank 16 82 against 112)
         launch_kernel((proj_act_kernel<1, 1>), dim3((p.N + 15) / 16, (p.M + 15) / 16), dim3(64 * kActWaves), 0, stream, p);
-    } else if (p.yf && p.K % 64 == 0 && (long long)((p.M + 63) / 64) * ((p.N + 47) / 48) <= 256) {
+    } else if ((long long)((p.M + 63) / 64) * ((p.N + 47) / 48) <= 256) {
         // one round of 64 x 48 tiles: 8192 rows at rank 32 501 -> 484 us a call;
         // with two rounds no gain or slower (12000 rows at rank 64 621 -> 647)
         launch_kernel((proj_act_kernel<4, 3>), dim3((p.N + 47) / 48, (p.M + 63) / 64), dim3(64 * kActWaves), 0, stream, p);
-    } else if (p.yf && p.N <= 2 * kBN && p.M < 256 * kBM) {
+    } else if (p.N <= 2 * kBN && p.M < 256 * kBM) {
         // activation pass with fewer than 256 row tiles of 128: 32-row tiles
         // (every workgroup also reads all of A, so more tiles only pay
         // until the grid covers the compute units; measured 80 -> 66 us at
