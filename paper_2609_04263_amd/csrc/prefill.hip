@@ -1408,6 +1408,11 @@ Kernel pick(int kg)
 // format's costs two to three times as much).  Measured at B = 1, C = 32 of
 // 8192 tokens: 30 to 70 us fused against 220 to 470; at B = 8, C = 200 of 3000
 // and D = 128: 250 against 152.
+// At D = 64 the LDS holds two workgroups per CU: together they take 1.4 times
+// as long per block as one alone, so more ranges than 256 workgroups need
+// still pay while each has eight blocks or more (32 query heads on 4, 4-bit:
+// B = 2, C = 300 of 8000 tokens 246 -> 118 us, B = 8, C = 64 of 3000 56 -> 45;
+// with ranges down to four blocks B = 8, C = 40 of 700 went 22.0 -> 23.8).
 template <int D>
 int fused_splits(const AttnParams& p)
 {
@@ -1416,18 +1421,29 @@ int fused_splits(const AttnParams& p)
     const long long units = (long long)p.B * p.H, rows = (long long)p.C * p.G, nb = p.pf_nvb;
     const double dq = D == 64 ? 0.004 : D == 128 ? 0.007 : 0.0106, a = D == 64 ? 1.0 : D == 128 ? 1.15 : 1.9;  // us
     const double f = p.rotate ? (D == 64 ? 1.7 : D == 128 ? 3.1 : 5.7) : (D == 64 ? 1.0 : D == 128 ? 1.3 : 2.2);
+    const double f2 = p.rotate ? 2.3 : 1.4;  // two workgroups per CU, D = 64
     const auto rounds = [](long long wgs, int at_once) { return (double)((wgs + at_once - 1) / at_once); };
     const double image = units * nb * dq + nb * a * rounds(units * ((rows + kRows - 1) / kRows), D == 64 ? 512 : 256);
     // Key ranges: to fill the CUs, at least four blocks each, and their
     // partials (the first range's outputs wait in O itself) within the units'
     // shares of the workspace
     const long long wgs = units * ((rows + kFusedRows - 1) / kFusedRows);
-    long long S = 256 / wgs < nb / 4 ? 256 / wgs : nb / 4;
-    while (S > 1 && (S - 1) * rows * D * 4 + S * rows * 8 > nb * image_bytes<D>())
-        --S;
-    S = S < 1 ? 1 : S;
-    const double fused = (S > 1 ? 10.0 : 0.0) + (double)((nb + S - 1) / S) * f * rounds(wgs * S, 256);
-    return fused < image ? (int)S : 0;
+    const auto ranges = [&](int at_once, int least) {
+        long long S = at_once / wgs < nb / least ? at_once / wgs : nb / least;
+        while (S > 1 && (S - 1) * rows * D * 4 + S * rows * 8 > nb * image_bytes<D>())
+            --S;
+        return S < 1 ? 1 : S;
+    };
+    const auto cost = [&](long long S) {
+        const double block = D == 64 && wgs * S > 256 ? f2 * rounds(wgs * S, 512) : f * rounds(wgs * S, 256);
+        return (S > 1 ? 10.0 : 0.0) + (double)((nb + S - 1) / S) * block;
+    };
+    long long S = ranges(256, 4);
+    if (D == 64) {
+        const long long two = ranges(512, 8);
+        S = cost(two) < cost(S) ? two : S;
+    }
+    return cost(S) < image ? (int)S : 0;
 }
 
 template <int D, int KG, bool W8, bool ROT>

@@ -32,6 +32,14 @@ def test_fused_tile_edges(name, C):
     run(name, B=1, H=2, G=4, n=400 + C, C=C, seed=420 + C)
 
 
+@pytest.mark.parametrize("name", ["tiny_b16", "had_d64_g32"])
+@pytest.mark.parametrize("shape", [dict(B=8, n=1001, C=65), dict(B=36, n=299, C=20)], ids=["ranges", "one_range"])
+def test_fused_two_workgroups_per_cu(name, shape):
+    # head size 64: 128 tiles in four key ranges of eight blocks, the last
+    # block partial, and 288 tiles of one range each
+    run(name, H=8, G=2, seed=425, **shape)
+
+
 @pytest.mark.parametrize("name", NAMES)
 def test_workspace_tiles(name):
     # 32 units of 1 + 4 tiles of 256 rows: the workspace path at every head size
