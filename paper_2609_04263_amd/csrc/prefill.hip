@@ -754,6 +754,8 @@ __global__ __launch_bounds__(kDqThreads) void dequant_kernel(AttnParams p)
 // (lds_addr wave-uniform, held in M0 while the copy issues).  Inline
 // assembly, so that the compiler does not make LDS reads wait for every
 // outstanding copy; the kernel's own vmcnt waits order them.
+// The hardware needs one wait state between a scalar write of M0 and an LDS
+// load that reads it; inside an assembly string the compiler adds none.
 __device__ __forceinline__ void copy16(uint64_t base, uint32_t voff, uint32_t lds_addr)
 {
     const uint32_t m0v = __builtin_amdgcn_readfirstlane(lds_addr);
@@ -762,7 +764,7 @@ __device__ __forceinline__ void copy16(uint64_t base, uint32_t voff, uint32_t ld
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)base);
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
     const uint64_t sb = ((uint64_t)hi << 32) | (uint64_t)lo;
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(m0v), "v"(voff), "s"(sb) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(m0v), "v"(voff), "s"(sb) : "memory");
 }
 
 // s_waitcnt vmcnt(n) for a wave-uniform n (expcnt and lgkmcnt not waited)

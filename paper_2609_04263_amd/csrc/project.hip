@@ -1067,10 +1067,12 @@ __device__ __forceinline__ int pp_swz(int row)
 // (lds_addr wave-uniform, held in M0 while the copy issues).  Inline
 // assembly, so that the compiler does not make LDS reads wait for every
 // outstanding copy; the kernel's own vmcnt waits order them.
+// The hardware needs one wait state between a scalar write of M0 and an LDS
+// load that reads it; inside an assembly string the compiler adds none.
 __device__ __forceinline__ void pp_copy16(uint64_t base, uint32_t voff, uint32_t lds_addr)
 {
     const uint32_t m0v = __builtin_amdgcn_readfirstlane(lds_addr);
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(m0v), "v"(voff), "s"(base) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(m0v), "v"(voff), "s"(base) : "memory");
 }
 
 __global__ __launch_bounds__(kPThreads, 1) void proj_gemm_pp_kernel(ProjParams p)
