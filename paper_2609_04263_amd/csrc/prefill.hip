@@ -275,18 +275,17 @@ __device__ __forceinline__ void fwht_rows8(float* x, int lane, float c)
 // and binary16 must still hold it.
 constexpr float kRotKeyScale = 0.0625f;
 
-// fp32 -> fp16 hi + lo: hi is v with its mantissa cut to binary16 width, lo the
-// exact remainder, each rounded once (22 bits together).
-__device__ __forceinline__ void split_cut8(const float* v, half8* hi, half8* lo)
+// fp32 -> fp16 hi + lo, each rounded to nearest: |v - hi - lo| <= 2^-23 |v|
+// (2^-25 where lo is subnormal).  Cutting v to binary16 width for hi takes as
+// many operations, but leaves a remainder of up to a whole ulp: twice the error.
+__device__ __forceinline__ void split8(const float* v, half8* hi, half8* lo)
 {
-    float h[8], l[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        h[e] = __uint_as_float(__float_as_uint(v[e]) & 0xFFFFE000u);
-        l[e] = v[e] - h[e];
+        const _Float16 h = (_Float16)v[e];
+        (*hi)[e] = h;
+        (*lo)[e] = (_Float16)(v[e] - (float)h);
     }
-    *hi = pack_half8(h);
-    *lo = pack_half8(l);
 }
 
 // Where a rotated block's rows go back to the image: token tau's channels 8 P
@@ -295,7 +294,7 @@ template <int D>
 __device__ __forceinline__ void put_key(uint8_t* img, int tau, int P, const float* x)
 {
     half8 h, l;
-    split_cut8(x, &h, &l);
+    split8(x, &h, &l);
     *(u32x4*)(img + 512 * P + 16 * tau) = __builtin_bit_cast(u32x4, h);
     *(u32x4*)(img + klo_at<D>() + 512 * P + 16 * tau) = __builtin_bit_cast(u32x4, l);
 }
