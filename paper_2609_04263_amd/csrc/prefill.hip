@@ -11,7 +11,8 @@
 // groups' scales and offsets in place of the lo half.  A rotating format's
 // keys and values are rotated back to the original basis (an fp32 FWHT per
 // token in LDS) before they are rounded, so queries and outputs need no
-// rotation.  Two ways to the images, chosen by fused_splits:
+// rotation; its keys are scaled by a power of two per eight tokens (see
+// octet_exponent).  Two ways to the images, chosen by fused_splits:
 //
 //   workspace  dequant_kernel reconstructs every visible block of a unit
 //              once into the caller's workspace and attn_kernel streams the
@@ -270,10 +271,49 @@ __device__ __forceinline__ void fwht_rows8(float* x, int lane, float c)
     }
 }
 
-// Keys of a rotating format are kept at 2^-4 of their value: rotated back, an
-// outlier channel can be sqrt(D) <= 16 times the largest stored magnitude,
-// and binary16 must still hold it.
-constexpr float kRotKeyScale = 0.0625f;
+// Keys of a rotating format, eight tokens (an octet) at a time, are kept times a
+// power of two that brings them below 2^12.  Binary16's range then holds any
+// keys, and hi + lo is within 2^-23 of a key, or 2^-25 of the largest of its
+// octet.  (A fixed 2^-4 in its place left an absolute error of 2^-21: rms 3e-4
+// of keys of 1e-3, and keys from 2^20 on overflowed.)  The exponent comes from
+// the octet's largest stored magnitude M < 2^(ef - 126), ef the exponent field
+// of M: rotated back, a key is below sqrt(D) M <= 2^(ef - 122), and 2^(134 -
+// ef) of it below 2^12.  ef is rounded up to a multiple of four, so that a
+// block's four octets mostly share it and the softmax takes it as its factor;
+// where they differ, the scores are brought to the largest first.
+//
+// The image has no room for the exponents, but bit 14 of every lo half is
+// free: a lo half is at most 1 (half an ulp of a hi half below 2^12), and bit
+// 14 is set from 2 on.  Bit i of octet j's ef is bit 14 of the lo half of
+// token 8 j + i's channel D / 2, so a wave that has lo fragment D / 32 gathers
+// all four exponents by one ballot.
+//
+// It costs rotating formats 2 to 3.5% of a call.  A power per block from its
+// scales (no maximum over the keys) with one factor per block, or per key range
+// of the fused path, cost as much.
+constexpr uint32_t kExponentBit = 0x4000u;
+constexpr int kExponentBias = 134;
+
+// The value of lane l rotated by N within its 16-lane row
+template <int N>
+__device__ __forceinline__ uint32_t row_ror(uint32_t v)
+{
+    return __builtin_amdgcn_update_dpp(0, v, 0x120 + N, 0xF, 0xF, false);
+}
+
+// ef of the wave's largest |x| (mx: this lane's), from 8 to 252, so that
+// 2^(ef - 134) and its inverse are normal numbers.
+__device__ __forceinline__ int octet_exponent(float mx)
+{
+    uint32_t m = __float_as_uint(mx);  // not negative: ordered as integers
+    m = max(m, row_ror<8>(m));
+    m = max(m, row_ror<4>(m));
+    m = max(m, row_ror<2>(m));
+    m = max(m, row_ror<1>(m));
+    const uint32_t a = max((uint32_t)__builtin_amdgcn_readlane(m, 0), (uint32_t)__builtin_amdgcn_readlane(m, 16));
+    const uint32_t b = max((uint32_t)__builtin_amdgcn_readlane(m, 32), (uint32_t)__builtin_amdgcn_readlane(m, 48));
+    return min(max((int)((max(a, b) >> 23) + 3) & ~3, 8), 252);
+}
 
 // fp32 -> fp16 hi + lo, each rounded to nearest: |v - hi - lo| <= 2^-23 |v|
 // (2^-25 where lo is subnormal).  Cutting v to binary16 width for hi takes as
@@ -289,27 +329,34 @@ __device__ __forceinline__ void split8(const float* v, half8* hi, half8* lo)
 }
 
 // Where a rotated block's rows go back to the image: token tau's channels 8 P
-// .. 8 P + 7 of the keys, and channel d of octet wv's values.
+// .. 8 P + 7 of the keys (mark: or'ed into the first lo half), and channel d of
+// octet wv's values.
 template <int D>
-__device__ __forceinline__ void put_key(uint8_t* img, int tau, int P, const float* x)
+__device__ __forceinline__ void put_key(uint8_t* img, int tau, int P, const float* x, uint32_t mark = 0u)
 {
     half8 h, l;
     split8(x, &h, &l);
+    u32x4 lw = __builtin_bit_cast(u32x4, l);
+    lw.x |= mark;
     *(u32x4*)(img + 512 * P + 16 * tau) = __builtin_bit_cast(u32x4, h);
-    *(u32x4*)(img + klo_at<D>() + 512 * P + 16 * tau) = __builtin_bit_cast(u32x4, l);
+    *(u32x4*)(img + klo_at<D>() + 512 * P + 16 * tau) = lw;
 }
 
+// mx: the largest magnitude this lane put into the rows.
 template <int D>
-__device__ __forceinline__ void rotate_keys(const AttnParams& p, uint8_t* img, float* rows, int wv, int lane)
+__device__ __forceinline__ void rotate_keys(const AttnParams& p, uint8_t* img, float* rows, float mx, int wv, int lane)
 {
     constexpr int PT = scratch_pitch<D>();
-    fwht_rows8<D>(rows, lane, p.rot_c * kRotKeyScale);
+    const int ef = octet_exponent(mx);
+    fwht_rows8<D>(rows, lane, p.rot_c * __uint_as_float((uint32_t)(127 + kExponentBias - ef) << 23));
 #pragma unroll
     for (int i = lane; i < D; i += 64) {
         const float* src = rows + (i & 7) * PT + 8 * (i >> 3);
         const floatx4 a = *(const floatx4*)src, b = *(const floatx4*)(src + 4);
         const float x[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-        put_key<D>(img, 8 * wv + (i & 7), i >> 3, x);
+        // (piece D / 16 holds channel D / 2)
+        const bool mark = i >> 3 == D / 16 && ((ef >> (i & 7)) & 1);
+        put_key<D>(img, 8 * wv + (i & 7), i >> 3, x, mark ? kExponentBit : 0u);
     }
     lds_order();  // the values follow through the same rows
 }
@@ -467,11 +514,13 @@ struct Keys {
         }
     }
 
-    __device__ __forceinline__ void finish(const AttnParams& p, const Sections& s, uint8_t* img, float* scratch, int tid)
+    __device__ __forceinline__ void finish(const AttnParams& p, const Sections& s, int valid, uint8_t* img, float* scratch,
+                                           int tid)
     {
         const bool aff = AFF || p.k_mode == KVQ_AFFINE;
         constexpr float nh = -(float)(1 << (BITS - 1));
         const int lane = tid & 63, wv = tid >> 6, t = tau(tid);
+        float mx = 0.0f;
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             const int P = chunk(tid, i);
@@ -487,6 +536,15 @@ struct Keys {
                 x[e] = fmaf(x[e], sc[m][k], aff ? z[m][k] : nh * sc[m][k]);
             }
             if constexpr (ROT) {
+                // (what dead tokens hold must not set the octet's exponent)
+                if (valid < 32) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        x[e] = t < valid ? x[e] : 0.0f;
+                }
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    mx = fmaxf(mx, fabsf(x[e]));
                 float* dst = scratch + t * PT + 8 * P;
                 *(floatx4*)dst = floatx4{x[0], x[1], x[2], x[3]};
                 *(floatx4*)(dst + 4) = floatx4{x[4], x[5], x[6], x[7]};
@@ -495,7 +553,7 @@ struct Keys {
             }
         }
         if constexpr (ROT)
-            rotate_keys<D>(p, img, scratch + wv * 8 * PT, wv, lane);
+            rotate_keys<D>(p, img, scratch + wv * 8 * PT, mx, wv, lane);
         if constexpr (CK) {
             // The scales (fp32, in place of the lo half) are kept as ratios
             // s[g] / s[g + 1], the last group's as it is: the score sum over
@@ -599,7 +657,7 @@ __device__ __forceinline__ void coded_blocks(const AttnParams& p, const Sections
     Values<D, VB, M16, AFF, ROT> v;
     k.load(p, s, tid);
     v.load(p, s, tid);
-    k.finish(p, s, img, scratch, tid);
+    k.finish(p, s, valid, img, scratch, tid);
     v.finish(p, valid, img, scratch, tid);
 }
 
@@ -674,6 +732,7 @@ __device__ __forceinline__ void fp16_image(const AttnParams& p, const uint16_t* 
 #pragma unroll
         for (int e = 0; e < 8; ++e)
             vw[i][e] = row[e] >= 0 ? vr[(size_t)row[e] * D + lane + 64 * i] : (uint16_t)0;
+    float mx = 0.0f;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
         const int P = K::chunk(tid, i);
@@ -681,15 +740,17 @@ __device__ __forceinline__ void fp16_image(const AttnParams& p, const uint16_t* 
             const uint32_t w[4] = {kw[i].x, kw[i].y, kw[i].z, kw[i].w};
             float* dst = scratch + t * PT + 8 * P;
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
+            for (int e = 0; e < 8; ++e) {
                 dst[e] = f16_bits_to_f32((uint16_t)(w[e >> 1] >> (16 * (e & 1))));
+                mx = fmaxf(mx, fabsf(dst[e]));
+            }
         } else {
             *(u32x4*)(img + 512 * P + 16 * t) = kw[i];
             *(u32x4*)(img + klo_at<D>() + 512 * P + 16 * t) = u32x4{0u, 0u, 0u, 0u};
         }
     }
     if constexpr (ROT)
-        rotate_keys<D>(p, img, scratch + wv * 8 * PT, wv, lane);
+        rotate_keys<D>(p, img, scratch + wv * 8 * PT, mx, wv, lane);
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
         const int d = lane + 64 * i;
@@ -831,8 +892,9 @@ constexpr int kNoRow = -(1 << 30);  // position of a query row past the end: eve
 // One wave's state: 32 QT query rows (columns of the MFMAs: column l % 32 of
 // tile q is row r0 + 32 (QT wave + q) + l % 32).  KG: key group size / 32 when
 // the format's keys have per-token groups (code blocks then take exact code
-// operands), 0 otherwise.
-template <int D, int KG, int QT>
+// operands), 0 otherwise.  ROT: a rotating format (KG = 0), whose keys carry an
+// exponent per eight tokens.
+template <int D, int KG, int QT, bool ROT>
 struct Wave {
     static constexpr int NK = D / 16, NT = D / 32;        // K fragments, 32-channel value tiles
     static constexpr int KS = KG > 0 ? 2 * KG : NK;       // K fragments per group
@@ -846,6 +908,7 @@ struct Wave {
     float qz[QT][NZ];  // lane (col, h): the query's sum over group 2 j + h
     int qpos[QT];
     float sscale;      // scores times sscale are exponents (base 2)
+    float bscale;      // ROT: the same for the scores of the present block
     int first;         // position of the wave's oldest query when all its rows exist
     floatx16 acc[QT][NT];
     floatx16 s[QT];    // the scores of the block between scores() and update()
@@ -863,8 +926,6 @@ struct Wave {
         // zero or subnormal scale gives zero queries, zero scores, sscale 1)
         const float qscale = __uint_as_float(__float_as_uint(p.sm_log2) & 0xFF800000u);
         sscale = qscale == 0.0f ? 1.0f : p.sm_log2 / qscale;
-        if (p.rotate)
-            sscale *= 1.0f / kRotKeyScale;
         sscale = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sscale)));  // a scalar register
         const int first_pos = p.n - p.C, wrow0 = t.r0 + 32 * QT * wave;
         first = __builtin_amdgcn_readfirstlane(wrow0 + 32 * QT <= t.rows ? first_pos + wrow0 / p.G : kNoRow);
@@ -984,6 +1045,7 @@ struct Wave {
         } else {
             constexpr int PH = PF / 2;
             half8 fh[PH], fl[PH];
+            uint32_t ef = 0;  // ROT: the octets' exponents, a byte each
 #pragma unroll
             for (int k = 0; k < PH; ++k) {
                 fh[k] = frag(1024 * k);
@@ -992,6 +1054,14 @@ struct Wave {
 #pragma unroll
             for (int k = 0; k < NK; ++k) {
                 hook(k);
+                if constexpr (ROT) {
+                    if (k == NK / 2) {
+                        u32x4 w = __builtin_bit_cast(u32x4, fl[k % PH]);
+                        ef = (uint32_t)__ballot((w.x & kExponentBit) != 0);
+                        w.x &= ~kExponentBit;
+                        fl[k % PH] = __builtin_bit_cast(half8, w);
+                    }
+                }
 #pragma unroll
                 for (int c = 0; c < QT; ++c) {
                     const half8 qk = k < NK - QL ? q[c][k] : fq[k - (NK - QL)];
@@ -1005,6 +1075,26 @@ struct Wave {
                     fl[k % PH] = frag(klo_at<D>() + 1024 * (k + PH));
                 }
                 __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (ROT) {
+                int top = (int)(ef & 0xFFu);
+                if (ef != (uint32_t)top * 0x01010101u) {
+#pragma unroll
+                    for (int j = 1; j < 4; ++j)
+                        top = max(top, (int)(ef >> (8 * j) & 0xFFu));
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        // octet j is the elements 4 j .. 4 j + 3
+                        const int d = 127 + (int)(ef >> (8 * j) & 0xFFu) - top;
+                        const float f = __uint_as_float((uint32_t)max(d, 0) << 23);
+#pragma unroll
+                        for (int c = 0; c < QT; ++c)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i)
+                                s[c][4 * j + i] *= f;
+                    }
+                }
+                bscale = __uint_as_float(__float_as_uint(sscale) + ((uint32_t)(top - kExponentBias) << 23));
             }
         }
     }
@@ -1048,7 +1138,7 @@ struct Wave {
 #pragma unroll
             for (int e = 1; e < 16; ++e)
                 lm[c] = fmaxf(lm[c], s[c][e]);
-            lm[c] *= sscale;
+            lm[c] *= ROT ? bscale : sscale;
             up = up || lm[c] > m[c] + 8.0f;
         }
         if (__any(up)) {
@@ -1077,7 +1167,7 @@ struct Wave {
                 float pv[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    pv[e] = fast_exp2(fmaf(s[c][8 * u + e], sscale, -mn));
+                    pv[e] = fast_exp2(fmaf(s[c][8 * u + e], ROT ? bscale : sscale, -mn));
                     ps += pv[e];
                 }
                 ph[c][u] = pack_half8(pv);
@@ -1141,7 +1231,7 @@ __device__ __forceinline__ int xcd_item()
 }
 
 // NW waves per workgroup, 32 QT NW query rows per tile.
-template <int D, int KG, int NW>
+template <int D, int KG, int NW, bool ROT>
 __global__ __launch_bounds__(64 * NW, D == 256 && NW == 4 ? 1 : 2) void attn_kernel(AttnParams p)
 {
     constexpr int QT = qtiles<D>();
@@ -1155,7 +1245,7 @@ __global__ __launch_bounds__(64 * NW, D == 256 && NW == 4 ? 1 : 2) void attn_ker
     // the longest (newest) tiles of a unit start first
     const int L = xcd_item(), uloc = __builtin_amdgcn_readfirstlane(L / p.pf_tiles);
     const Tile t = make_tile(p, p.pf_u0 + uloc, p.pf_tiles - 1 - (L - uloc * p.pf_tiles), 32 * QT * NW);
-    Wave<D, KG, QT> w;
+    Wave<D, KG, QT, ROT> w;
     w.init(p, t, plds + NST * BI, wave, lane);
 
     const uint32_t lbase = (uint32_t)(uintptr_t)plds;
@@ -1263,7 +1353,7 @@ __global__ __launch_bounds__(kFusedThreads, 2) void fused_kernel(AttnParams p)
             asm volatile("" ::: "memory");
             __builtin_amdgcn_sched_barrier(0);
         };
-        Wave<D, KG, 1> w;
+        Wave<D, KG, 1, ROT> w;
         w.init(p, t, plds + LD::kQuery, wave, lane);
         sync();
         sync();
@@ -1389,14 +1479,15 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(AttnParams p)
 typedef void (*Kernel)(AttnParams);
 
 template <int D>
-Kernel pick(int kg)
+Kernel pick(int kg, bool rot)
 {
     constexpr int NW = waves<D>();
-    return kg == 1   ? attn_kernel<D, (D >= 256 ? 0 : 1), NW>
-           : kg == 2 ? attn_kernel<D, 2, NW>
-           : kg == 4 ? attn_kernel<D, (D >= 128 ? 4 : 1), NW>
-           : kg == 8 ? attn_kernel<D, (D >= 256 ? 8 : 1), NW>
-                     : attn_kernel<D, 0, NW>;
+    return rot       ? attn_kernel<D, 0, NW, true>
+           : kg == 1 ? attn_kernel<D, (D >= 256 ? 0 : 1), NW, false>
+           : kg == 2 ? attn_kernel<D, 2, NW, false>
+           : kg == 4 ? attn_kernel<D, (D >= 128 ? 4 : 1), NW, false>
+           : kg == 8 ? attn_kernel<D, (D >= 256 ? 8 : 1), NW, false>
+                     : attn_kernel<D, 0, NW, false>;
 }
 
 // Key ranges per query tile on the fused path, or 0 for the workspace path.
@@ -1511,7 +1602,7 @@ hipError_t launch(const AttnParams& p0, size_t ws_bytes, hipStream_t stream)
     }
     void (*deq)(AttnParams) = w8 ? (rot ? dequant_kernel<D, true, true> : dequant_kernel<D, true, false>)
                                  : (rot ? dequant_kernel<D, false, true> : dequant_kernel<D, false, false>);
-    Kernel att = pick<D>(rot ? 0 : kg);
+    Kernel att = pick<D>(kg, rot);
     int nw = waves<D>(), per = kRows;
     if constexpr (D == 256) {
         // hi + lo keys at D = 256 are bound by LDS reads (48 KiB per wave and
@@ -1519,7 +1610,7 @@ hipError_t launch(const AttnParams& p0, size_t ws_bytes, hipStream_t stream)
         // cover the CUs, four waves of 128 rows (measured at 64 such tiles:
         // 265 -> 232 us; with code blocks no gain)
         if ((rot || kg <= 1) && units * ((rows + kRows - 1) / kRows) <= 128) {
-            att = attn_kernel<D, 0, 4>;
+            att = rot ? attn_kernel<D, 0, 4, true> : attn_kernel<D, 0, 4, false>;
             nw = 4;
             per = 128;
         }

@@ -28,13 +28,17 @@ FORMATS = {
 B, H, G, N, C = 4, 8, 4, 293, 260  # 32 units of 1040 rows: the workspace path at every head size
 
 
+def scaled_kv(seed, B, n, H, D, scale):
+    """Keys times powers of two (exact in bf16; one, or one per token), and values."""
+    K, V = synth.kv_tokens(seed, B, n, H, D)
+    return synth.to_bf16_bits(synth.bf16_bits_to_f32(K) * np.asarray(scale, dtype=np.float32).reshape(1, -1, 1, 1)), V
+
+
 def images(name, seed, scale=1.0):
     """The oracle's cache, and the bits of the images' key halves hi and lo, [B, H, blocks, 32, D]."""
     from paper_2609_04263_amd import kvq
     fmt, D = FORMATS[name]
-    K, V = synth.kv_tokens(seed, B, N, H, D)
-    if scale != 1.0:  # a power of two, exact
-        K = synth.to_bf16_bits((K.astype(np.uint32) << 16).view(np.float32) * np.float32(scale))
+    K, V = scaled_kv(seed, B, N, H, D, scale)
     ref = oracle.Cache(fmt, B, H, D, N)
     ref.append(K, V)
     gc = kvq.Cache(fmt, B, H, D, N)
@@ -70,3 +74,102 @@ def test_hi_lo_keys(name):
     bound = (2.0 ** -23 + 2.0 ** -24) * np.abs(k) + 2.0 ** -25
     over = np.abs(got - k) > bound
     assert not over.any(), f"{name}: {over.sum()} of {k.size} keys"
+
+
+ROTATING = {
+    "hadamard": CASES["hadamard"],
+    "had_affine_window": CASES["had_affine_window"],
+    "kvarn_sink": CASES["kvarn_sink"],
+    "had_d64_g32": (configs.make_format(4, 4, k_group=32, v_group=32, rotate=64), 64),
+    "had8_d128": (configs.make_format(8, 8, k_group=64, v_group=64, rotate=128), 128),
+    "had_perch_window": (configs.make_format(4, 2, k_axis=1, k_group=32, v_group=32, residual=32, flush=32,
+                                             rotate=128), 128),
+}
+FORMATS.update(ROTATING)
+
+
+def fwht64(x):
+    """The normalized Hadamard transform of the last axis in 64 bits."""
+    D = x.shape[-1]
+    h = 1
+    while h < D:
+        v = x.reshape(*x.shape[:-1], D // (2 * h), 2, h)
+        x = np.stack((v[..., 0, :] + v[..., 1, :], v[..., 0, :] - v[..., 1, :]), axis=-2).reshape(x.shape)
+        h *= 2
+    return x / np.sqrt(D)
+
+
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** -14, 2.0 ** 9])
+@pytest.mark.parametrize("name", list(ROTATING))
+def test_rotated_keys_keep_their_precision_at_any_magnitude(name, scale):
+    ref, hi, lo = images(name, seed=910, scale=scale)
+    D = hi.shape[-1]
+    # octet j's exponent: bit 14 of the lo halves of channel D / 2 of its eight tokens
+    octets = (B, H, -1, 8)
+    bits = ((lo[..., D // 2] >> 14) & 1).reshape(octets).astype(np.int64)
+    ef = (bits << np.arange(8)).sum(axis=-1).repeat(8, axis=-1)
+    lo = lo.copy()
+    lo[..., D // 2] &= 0xBFFF
+    assert np.abs(f64(lo)).max() <= 1.0 and np.abs(f64(hi)).max() <= 4096.0
+    got = (f64(hi) + f64(lo)).reshape(B, H, -1, D) * 2.0 ** (ef[..., None] - 134.0)
+    want = np.zeros_like(got)
+    want[:, :, :N] = fwht64(ref.dequant()[0])  # (stored rotated)
+    octet_max = np.abs(want).max(axis=-1).reshape(octets).max(axis=-1).repeat(8, axis=-1)
+    # the split; then a transform in fp32 (log2 D stages and the product, each
+    # rounding within 2^-24 of the vector's length) of keys rounded once
+    length = np.sqrt((want ** 2).sum(axis=-1, keepdims=True))
+    bound = 2.0 ** -23 * np.abs(want) + 2.0 ** -25 * octet_max[..., None] + (np.log2(D) + 2) * 2.0 ** -24 * length
+    over = np.abs(got - want) > bound
+    assert not over.any(), f"{name}: {over.sum()} of {want.size} keys"
+
+
+SHAPES = pytest.mark.parametrize("shape", [dict(b=1, h=1, g=2, n=1493, c=23), dict(b=B, h=H, g=G, n=N, c=C)],
+                                 ids=["fused", "workspace"])
+
+
+def relative_error(name, seed, scale, sm, b, h, g, n, c):
+    from paper_2609_04263_amd import kvq
+    fmt, D = FORMATS[name]
+    K, V = scaled_kv(seed, b, n, h, D, scale)
+    ref = oracle.Cache(fmt, b, h, D, n)
+    ref.append(K, V)
+    gc = kvq.Cache(fmt, b, h, D, n)
+    gc.append(dev_bf16(K), dev_bf16(V))
+    Q = synth.normal_bf16(seed, ("chunk-q",), (b, c, h * g, D))
+    O = torch.empty((b, c, h * g, D), dtype=torch.float32, device="cuda")
+    gc.prefill_attn(dev_bf16(Q), c, h * g, sm / np.sqrt(D), O, gc.prefill_workspace())
+    want = ref.prefill_attn(Q, sm / np.sqrt(D))
+    return np.linalg.norm(O.cpu().numpy() - want) / np.linalg.norm(want)
+
+
+# Probabilities and values are rounded to binary16, 2^-11 each; nothing else may
+# show in the outputs.
+@SHAPES
+@pytest.mark.parametrize("name", list(ROTATING))
+def test_rotated_outputs_of_small_keys(name, shape):
+    # the scores of ordinary keys, from keys of 2^-14 and a softmax scale of 2^14
+    assert relative_error(name, 920, 2.0 ** -14, 2.0 ** 14, **shape) <= 2.0 ** -10
+
+
+@SHAPES
+@pytest.mark.parametrize("name", list(ROTATING))
+def test_rotated_outputs_of_mixed_magnitudes(name, shape):
+    # octets with different exponents in one block
+    scale = 2.0 ** -(5.0 * (np.arange(shape["n"]) // 8 % 3))
+    assert relative_error(name, 925, scale, 1.0, **shape) <= 2.0 ** -10
+
+
+def test_rotated_keys_beyond_binary16():
+    # codes and scales hold keys of 2^20; a softmax that one key takes whole
+    from paper_2609_04263_amd import kvq
+    fmt, D = FORMATS["hadamard"]
+    K, V = scaled_kv(930, 1, 320, 2, D, 2.0 ** 20)
+    ref = oracle.Cache(fmt, 1, 2, D, 320)
+    ref.append(K, V)
+    gc = kvq.Cache(fmt, 1, 2, D, 320)
+    gc.append(dev_bf16(K), dev_bf16(V))
+    Q = synth.normal_bf16(931, ("chunk-q",), (1, 40, 4, D))
+    O = torch.empty((1, 40, 4, D), dtype=torch.float32, device="cuda")
+    gc.prefill_attn(dev_bf16(Q), 40, 4, 1.0, O, gc.prefill_workspace())
+    assert torch.isfinite(O).all()
+    assert_close(O.cpu().numpy(), ref.prefill_attn(Q, 1.0), what="keys of 2^20")
