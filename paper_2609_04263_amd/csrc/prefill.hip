@@ -555,17 +555,13 @@ struct Keys {
         if constexpr (ROT)
             rotate_keys<D>(p, img, scratch + wv * 8 * PT, mx, wv, lane);
         if constexpr (CK) {
-            // The scales (fp32, in place of the lo half) are kept as ratios
-            // s[g] / s[g + 1], the last group's as it is: the score sum over
-            // groups is then one chain of products, its running sum moved from
-            // one group's scale to the next (scales are never zero: the code's
-            // floor is 1e-8, 2^-24 in fp16).  Then the offsets z'.
+            // the scales s (fp32, in place of the lo half), then the offsets z'
             const int n = 32 * (D >> (31 - __builtin_clz(p.k_group)));
             const uint8_t* sz = aff ? s.kz : s.ks;
             float* ms = (float*)(img + klo_at<D>());
             for (int i = tid; i < n; i += 256) {
                 const float s0 = meta_1<M16>(s.ks, i), z0 = meta_1<M16>(sz, i);
-                ms[i] = i + 32 < n ? s0 / meta_1<M16>(s.ks, i + 32) : s0;
+                ms[i] = s0;
                 ms[n + i] = aff ? z0 : nh * s0;
             }
         }
@@ -998,35 +994,63 @@ struct Wave {
             const float* ms = (const float*)(img + klo_at<D>()) + 4 * hf;
             auto scale = [&](int g, int j) { return *(const floatx4*)(ms + 32 * g + 8 * j); };
             half8 f[PF];
-            floatx4 sc[4];
+            floatx16 g[QT];
+            const auto offsets = [&] {
+#pragma unroll
+                for (int j = 0; j < NZ; ++j) {
+                    float za = ms[32 * NG + 32 * min(2 * j + hf, NG - 1) + (lane & 31) - 4 * hf];
+                    za = 2 * j + hf < NG ? za : 0.0f;
+#pragma unroll
+                    for (int c = 0; c < QT; ++c)
+                        s[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(za, qz[c][j], s[c], 0, 0, 0);
+                }
+            };
 #pragma unroll
             for (int k = 0; k < PF; ++k)
                 f[k] = frag(1024 * k);
+            // One sum per group, then one FMA by its scale as stored.  (A single
+            // sum moved from each group's scale to the next by their ratio
+            // takes 16 registers less, but has twice the rounding error: 1.8e-7
+            // against 0.8e-7 of a score at D = 256 with four groups.)  At D =
+            // 256 the registers do not hold the scales ahead: half are read
+            // beside the group's last product, half after it, and the offsets
+            // come last, 2 to 4% slower than the ratios.
+            constexpr bool kLate = D == 256;
+            floatx4 sc[4];
+            if (!kLate) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                sc[j] = scale(0, j);
+                for (int j = 0; j < 4; ++j)
+                    sc[j] = scale(0, j);
+                offsets();
+            }
 #pragma unroll
             for (int k = 0; k < NK; ++k) {
                 hook(k);
+                if (kLate && k % KS == KS - 1) {
+                    sc[0] = scale(k / KS, 0);
+                    sc[1] = scale(k / KS, 1);
+                }
 #pragma unroll
                 for (int c = 0; c < QT; ++c)
-                    s[c] = mfma32(f[k % PF], k < NK - QL ? q[c][k] : fq[k - (NK - QL)], s[c]);
+                    g[c] = mfma32(f[k % PF], k < NK - QL ? q[c][k] : fq[k - (NK - QL)], k % KS == 0 ? floatx16{} : g[c]);
                 if (k + PF >= NK - QL && k + PF < NK)
                     fq[k + PF - (NK - QL)] = query(k + PF);
                 if (k + PF < NK)
                     f[k % PF] = frag(1024 * (k + PF));
                 __builtin_amdgcn_sched_barrier(0);
                 if (k % KS == KS - 1) {
-                    // from group g's scale to the next group's (or out)
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
+                        const floatx4 v = kLate && j >= 2 ? scale(k / KS, j) : sc[j];
 #pragma unroll
                         for (int c = 0; c < QT; ++c)
 #pragma unroll
                             for (int i = 0; i < 4; ++i)
-                                s[c][4 * j + i] *= sc[j][i];
+                                s[c][4 * j + i] = kLate && k < KS ? v[i] * g[c][4 * j + i] : fmaf(v[i], g[c][4 * j + i], s[c][4 * j + i]);
+                        if (kLate && j & 1)
+                            __builtin_amdgcn_sched_barrier(0);
                     }
-                    if (k + 1 < NK) {
+                    if (!kLate && k + 1 < NK) {
 #pragma unroll
                         for (int j = 0; j < 4; ++j)
                             sc[j] = scale(k / KS + 1, j);
@@ -1034,14 +1058,8 @@ struct Wave {
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
-#pragma unroll
-            for (int j = 0; j < NZ; ++j) {
-                float za = ms[32 * NG + 32 * min(2 * j + hf, NG - 1) + (lane & 31) - 4 * hf];
-                za = 2 * j + hf < NG ? za : 0.0f;
-#pragma unroll
-                for (int c = 0; c < QT; ++c)
-                    s[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(za, qz[c][j], s[c], 0, 0, 0);
-            }
+            if (kLate)
+                offsets();
         } else {
             constexpr int PH = PF / 2;
             half8 fh[PH], fl[PH];

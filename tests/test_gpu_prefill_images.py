@@ -173,3 +173,32 @@ def test_rotated_keys_beyond_binary16():
     gc.prefill_attn(dev_bf16(Q), 40, 4, 1.0, O, gc.prefill_workspace())
     assert torch.isfinite(O).all()
     assert_close(O.cpu().numpy(), ref.prefill_attn(Q, 1.0), what="keys of 2^20")
+
+
+CODED = {name: CASES[name] for name in ("tiny_b1", "tiny_b16", "affine2_g128", "gqa12b", "g256", "affine8", "tiny_meta16",
+                                        "sym4_window")}
+CODED["affine_g32_d128"] = (configs.make_format(4, 4, k_group=32, v_group=32), 128)
+FORMATS.update(CODED)
+
+
+@pytest.mark.parametrize("name", list(CODED))
+def test_code_blocks_keep_scales_and_offsets_as_stored(name):
+    # a code block's lo half: the groups' scales, then their offsets, each the
+    # stored value in fp32, so that a score takes one rounding per group
+    ref, _, lo = images(name, seed=950)
+    fmt, D = FORMATS[name]
+    ng, blocks = D // fmt["k_group"], (ref.n_coded + 31) // 32
+    meta = np.float16 if fmt["meta_fp16"] else np.float32
+
+    def stored(section):
+        return ref.section(section).view(meta).reshape(B, H, -1, 32 * ng)[:, :, :blocks].astype(np.float32)
+
+    # part() put the bytes in token order: back to the order of the image
+    raw = lo.reshape(B, H, -1, 32, D // 8, 8).transpose(0, 1, 2, 4, 3, 5).reshape(B, H, -1, 32 * D)
+    got = np.ascontiguousarray(raw).view(np.float32)[:, :, :blocks]
+    live = np.arange(32 * blocks).reshape(blocks, 1, 32) < ref.n_coded
+    live = np.broadcast_to(live, (blocks, ng, 32)).reshape(blocks, 32 * ng)
+    s = stored(1)
+    z = stored(2) if fmt["k_mode"] == 0 else -np.float32(2 ** (fmt["k_bits"] - 1)) * s
+    assert (got[..., :32 * ng] == s)[:, :, live].all()
+    assert (got[..., 32 * ng:64 * ng] == z)[:, :, live].all()
