@@ -786,27 +786,9 @@ static void prefill_blocks(const kvq_cache* c, int* nsb, int* nvb)
     *nvb = *nsb + (tail + 31) / 32;
 }
 
-kvq_status kvq_prefill_workspace_bytes(const kvq_cache* c, size_t* bytes)
+// Everything of a chunked prefill's parameters but its buffers.
+static kvq::AttnParams prefill_params(const kvq_cache* c, int C, int H_q, float sm_scale)
 {
-    if (!c || !bytes)
-        return KVQ_ERR_ARG;
-    int nsb, nvb;
-    prefill_blocks(c, &nsb, &nvb);
-    *bytes = (size_t)c->B * c->H * nvb * kvq::prefill_image_bytes(c->D);
-    return KVQ_OK;
-}
-
-kvq_status kvq_prefill_attn(const kvq_cache* c, const void* Q, int C, int H_q, float sm_scale, void* O,
-                            void* workspace, size_t ws_bytes, void* stream)
-{
-    if (!c || !Q || !O || !aligned16(Q) || !aligned16(O) || !isfinite(sm_scale))
-        return KVQ_ERR_ARG;
-    if (H_q < c->H || H_q % c->H != 0 || C < 1 || C > c->n)
-        return KVQ_ERR_ARG;
-    int nsb, nvb;
-    prefill_blocks(c, &nsb, &nvb);
-    if (!workspace || !aligned16(workspace) || ws_bytes < (size_t)nvb * kvq::prefill_image_bytes(c->D))
-        return KVQ_ERR_WORKSPACE;
     const kvq_format& f = c->fmt;
     kvq::AttnParams p = {};
     p.nq = kvq::num_coded(f, c->n);
@@ -820,8 +802,6 @@ kvq_status kvq_prefill_attn(const kvq_cache* c, const void* Q, int C, int H_q, f
     p.vr = at<uint16_t>(c, 7);
     p.kq = at<uint16_t>(c, 8);
     p.vq = at<uint16_t>(c, 9);
-    p.q = (const uint16_t*)Q;
-    p.out = (float*)O;
     p.B = c->B;
     p.H = c->H;
     p.H_q = H_q;
@@ -845,9 +825,45 @@ kvq_status kvq_prefill_attn(const kvq_cache* c, const void* Q, int C, int H_q, f
     p.sm_log2 = sm_scale * 1.4426950408889634f;
     p.rot_c = rotation_constant(c->D);
     p.meta16 = f.meta_fp16;
+    prefill_blocks(c, &p.pf_nsb, &p.pf_nvb);
+    return p;
+}
+
+int kvq_internal_prefill_ranges(const kvq_cache* c, int C, int H_q)
+{
+    return kvq::prefill_ranges(prefill_params(c, C, H_q, 1.0f), c->D);
+}
+
+int kvq_internal_project_tile(int M, int N)
+{
+    return kvq::project_tile(M, N);
+}
+
+kvq_status kvq_prefill_workspace_bytes(const kvq_cache* c, size_t* bytes)
+{
+    if (!c || !bytes)
+        return KVQ_ERR_ARG;
+    int nsb, nvb;
+    prefill_blocks(c, &nsb, &nvb);
+    *bytes = (size_t)c->B * c->H * nvb * kvq::prefill_image_bytes(c->D);
+    return KVQ_OK;
+}
+
+kvq_status kvq_prefill_attn(const kvq_cache* c, const void* Q, int C, int H_q, float sm_scale, void* O,
+                            void* workspace, size_t ws_bytes, void* stream)
+{
+    if (!c || !Q || !O || !aligned16(Q) || !aligned16(O) || !isfinite(sm_scale))
+        return KVQ_ERR_ARG;
+    if (H_q < c->H || H_q % c->H != 0 || C < 1 || C > c->n)
+        return KVQ_ERR_ARG;
+    int nsb, nvb;
+    prefill_blocks(c, &nsb, &nvb);
+    if (!workspace || !aligned16(workspace) || ws_bytes < (size_t)nvb * kvq::prefill_image_bytes(c->D))
+        return KVQ_ERR_WORKSPACE;
+    kvq::AttnParams p = prefill_params(c, C, H_q, sm_scale);
+    p.q = (const uint16_t*)Q;
+    p.out = (float*)O;
     p.pf_ws = (uint8_t*)workspace;
-    p.pf_nvb = nvb;
-    p.pf_nsb = nsb;
     return kvq::launch_prefill(p, c->D, ws_bytes, (hipStream_t)stream) == hipSuccess ? KVQ_OK : KVQ_ERR_DEVICE;
 }
 

@@ -122,6 +122,9 @@ hipError_t launch_project_decode(const ProjParams& p, hipStream_t stream);
 // pass then writes t_hilo activations): 256x256 tiles that never straddle
 // Q, K and V, and a rank that is a multiple of 16.
 bool project_adapter_stages(int M, int d_in, int d_q, int d_kv, int rank);
+// Tile of the main pass over M > 32 rows and N outputs: 0 128x128, 1 128x64, 2
+// 64x64, -1 256x256.
+int project_tile(int M, int N);
 // Upper bound on the K slices of the decode path's partial adapter activations.
 constexpr int kProjTSlices = 16;
 // Workspace bytes of the projection for M rows and adapter rank r.
@@ -193,7 +196,15 @@ size_t decode_lds_bytes(int D, const kvq_format& f, int G);
 hipError_t launch_decode(const AttnParams& p, int D, hipStream_t stream);
 // Bytes of one reconstructed 32-token block (prefill workspace unit).
 size_t prefill_image_bytes(int D);
+// Key ranges per query tile on the fused path of a chunked prefill, 0 for the
+// workspace path.
+int prefill_ranges(const AttnParams& p, int D);
 // Chunked prefill over units in groups that fit ws_bytes (at least one unit).
 hipError_t launch_prefill(const AttnParams& p, int D, size_t ws_bytes, hipStream_t stream);
 
 }  // namespace kvq
+
+// The dispatch rules, for tests that have to know which kernels a call takes.
+// Host only; not part of the C ABI.
+extern "C" int kvq_internal_project_tile(int M, int N);
+extern "C" int kvq_internal_prefill_ranges(const kvq_cache* cache, int C, int H_q);

@@ -51,8 +51,6 @@
 // Sink tokens (fp16 rows) come first as blocks of their own; fp16 window
 // tokens past the coded ones are read from the ring.
 
-#include <atomic>
-
 #include "kvq_device.h"
 #include "kvq_internal.h"
 
@@ -896,7 +894,7 @@ struct Wave {
     static constexpr int KS = KG > 0 ? 2 * KG : NK;       // K fragments per group
     static constexpr int NG = NK / KS, NZ = (NG + 1) / 2;  // groups, offset MFMAs per tile
     static constexpr int PF = D == 256 ? 3 : 4;  // fragments read ahead (LDS latency)
-        // The last QL query fragments of a wave live in LDS (the 16 KiB that the
+    // The last QL query fragments of a wave live in LDS (the 16 KiB that the
     // ring leaves free at D = 256, where the registers do not hold them all).
     static constexpr int QL = query_lds_fragments<D, KG>();
     half8 q[QT][NK - QL];
@@ -1653,11 +1651,24 @@ hipError_t launch(const AttnParams& p0, size_t ws_bytes, hipStream_t stream)
 hipError_t launch_prefill_64(const AttnParams& p, size_t ws_bytes, hipStream_t stream);
 hipError_t launch_prefill_128(const AttnParams& p, size_t ws_bytes, hipStream_t stream);
 hipError_t launch_prefill_256(const AttnParams& p, size_t ws_bytes, hipStream_t stream);
+int prefill_ranges_64(const AttnParams& p);
+int prefill_ranges_128(const AttnParams& p);
+int prefill_ranges_256(const AttnParams& p);
 
 #if KVQ_PREFILL_D == 64
 hipError_t launch_prefill_64(const AttnParams& p, size_t ws_bytes, hipStream_t stream)
 {
     return pre::launch<64>(p, ws_bytes, stream);
+}
+
+int prefill_ranges_64(const AttnParams& p)
+{
+    return pre::fused_splits<64>(p);
+}
+
+int prefill_ranges(const AttnParams& p, int D)
+{
+    return D == 64 ? prefill_ranges_64(p) : D == 128 ? prefill_ranges_128(p) : prefill_ranges_256(p);
 }
 
 size_t prefill_image_bytes(int D)
@@ -1683,10 +1694,20 @@ hipError_t launch_prefill_128(const AttnParams& p, size_t ws_bytes, hipStream_t 
 {
     return pre::launch<128>(p, ws_bytes, stream);
 }
+
+int prefill_ranges_128(const AttnParams& p)
+{
+    return pre::fused_splits<128>(p);
+}
 #else
 hipError_t launch_prefill_256(const AttnParams& p, size_t ws_bytes, hipStream_t stream)
 {
     return pre::launch<256>(p, ws_bytes, stream);
+}
+
+int prefill_ranges_256(const AttnParams& p)
+{
+    return pre::fused_splits<256>(p);
 }
 #endif
 

@@ -1345,7 +1345,7 @@ __global__ __launch_bounds__(kPThreads, 1) void proj_gemm_pp_kernel(ProjParams p
 
 // -------------------------------------------------------------------- mid
 // M from 33 to about 2000 rows: tiles of 32 MI WM x 32 NI WN, one of a few
-// sizes chosen so that the tiles cover the compute units (mid_tile), WM x WN
+// sizes chosen so that the tiles cover the compute units (project_tile), WM x WN
 // waves of 32 MI x 32 NI each.  256x256 tiles leave most of the chip idle there
 // (48 workgroups at M = 333, N = 6144: 75 us of which each CU reads 4 MiB), and
 // a tile's time is bound by the LDS reads of its fragments and by the 100 to
@@ -1664,12 +1664,12 @@ void launch_mid(const ProjParams& p, hipStream_t stream)
 // 128x64, 2: 64x64), or -1 for the 256x256 tiles of the large-M kernel.  The
 // estimates (us at K = 4096; all scale with K) are fits to calls of 40 to 3000
 // rows at 2560, 6144 and 8192 outputs: one workgroup per CU for the 128x128
-// tiles (160 KiB ring), two for the smaller ones.  Measured (whole calls, 6144
+// tiles (128 KiB ring), two for the smaller ones.  Measured (whole calls, 6144
 // outputs, d_in 4096, rank 16; 128x128 / 128x64 / 64x64 / 256x256): 100 rows
 // 47.7 / 34.6 / 27.6 / -; 333 rows 48.1 / 43.3 / 50.0 / 82.4; 1024 rows 87.9 /
 // 75.2 / 88.9 / 85.3; 1500 rows 142 / 119 / 154 / 95.9.  (128x96 and 64x32 tiles
 // were within 4% of the best of these or slower everywhere.)
-static int mid_tile(int M, int N)
+int project_tile(int M, int N)
 {
     const auto tiles = [&](int bm, int bn) { return (double)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
     const double n0 = tiles(128, 128), n1 = tiles(128, 64), n2 = tiles(64, 64), n = tiles(256, 256);
@@ -1688,7 +1688,7 @@ static int mid_tile(int M, int N)
 
 bool project_adapter_stages(int M, int d_in, int d_q, int d_kv, int rank)
 {
-    return mid_tile(M, d_q + 2 * d_kv) < 0 && rank > 0 && rank % 16 == 0 && M >= kGM && d_q + 2 * d_kv >= kGN && d_in % kGK == 0 && d_q % kGN == 0 &&
+    return project_tile(M, d_q + 2 * d_kv) < 0 && rank > 0 && rank % 16 == 0 && M >= kGM && d_q + 2 * d_kv >= kGN && d_in % kGK == 0 && d_q % kGN == 0 &&
            d_kv % kGN == 0;
 }
 
@@ -1731,7 +1731,7 @@ hipError_t launch_project(const ProjParams& p, hipStream_t stream)
         return hipErrorInvalidValue;  // only the large-M pass reads bf16 hi / lo activations
     if (p.M <= 32 && !p.yf)
         return launch_project_decode(p, stream);
-    const int mid = p.yf || p.fuse || p.K % 64 != 0 ? -1 : mid_tile(p.M, p.N);
+    const int mid = p.yf || p.fuse || p.K % 64 != 0 ? -1 : project_tile(p.M, p.N);
     if (mid >= 0) {
         ProjParams q = p;
         q.nxcd = gemm_xcds();

@@ -1,7 +1,8 @@
 """The projection between the decode rows and the large prefill chunks.
 
-Rows at the edges of the 64- and 128-row tiles, output widths that leave
-partial and straddling column tiles, fewer K stages than the copy ring is deep,
+Rows at the edges of the tiles, output widths that leave partial and
+straddling column tiles (small shapes take 64x64 tiles, the larger ones assert
+theirs), fewer K stages than the copy ring is deep,
 and ranks that are not multiples of 16, against the fp64 oracle (2e-3 + 1e-2
 |ref|, as in test_gpu_project).  Without an adapter every output is one chain
 of products over K whichever kernel computes it, so a call's rows must equal
@@ -12,7 +13,7 @@ import pytest
 
 import oracle
 
-from gpu_util import assert_close
+from gpu_util import assert_close, project_tile
 from test_gpu_project import problem, run_gpu
 
 pytestmark = pytest.mark.gpu
@@ -27,10 +28,24 @@ def test_mid_rows_match_oracle(M, d_in, d_q, d_kv, r):
     assert_close(y, ref, what=f"M={M} d_in={d_in} d_q={d_q} d_kv={d_kv} r={r}")
 
 
-@pytest.mark.parametrize("M", [40, 200, 400, 900])
-def test_rows_do_not_depend_on_the_kernel(M):
+# tiles: 0 128x128, 1 128x64, 2 64x64, -1 256x256
+@pytest.mark.parametrize("tile,M,d_q,d_kv", [(1, 200, 3024, 576), (1, 250, 3024, 576), (0, 641, 4016, 752), (0, 765, 4016, 752)])
+@pytest.mark.parametrize("r", [16, 24, 64])
+def test_larger_tiles_match_oracle(tile, M, d_q, d_kv, r):
+    # partial row and column tiles, and column tiles that straddle Q, K and V
+    d_in = 128
+    assert project_tile(M, d_q + 2 * d_kv) == tile
+    H, W, A, Bm = problem(550 + M, M, d_in, d_q, d_kv, r)
+    y = run_gpu(H, W, A, Bm, r, 2.0, d_q, d_kv)
+    ref, _ = oracle.project(H, W, A, Bm, r, 2.0, d_q, d_kv)
+    assert_close(y, ref, what=f"M={M} d_q={d_q} d_kv={d_kv} r={r}")
+
+
+@pytest.mark.parametrize("tile,M", [(2, 40), (1, 200), (1, 400), (1, 900), (0, 641), (0, 700), (0, 768)])
+def test_rows_do_not_depend_on_the_kernel(tile, M):
     # 64x64, 128x64 and 128x128 tiles at 6144 outputs against 256x256 tiles
     d_in, d_q, d_kv = 512, 4096, 1024
+    assert project_tile(M, d_q + 2 * d_kv) == tile and project_tile(2304, d_q + 2 * d_kv) == -1
     H, W, A, Bm = problem(600, 2304, d_in, d_q, d_kv, 0)
     big = run_gpu(H, W, A, Bm, 0, 1.0, d_q, d_kv)
     assert np.array_equal(run_gpu(np.ascontiguousarray(H[:M]), W, A, Bm, 0, 1.0, d_q, d_kv), big[:M])
