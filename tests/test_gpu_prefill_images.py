@@ -12,7 +12,7 @@ import torch
 import oracle
 from paper_2609_04263_amd import configs, synth
 
-from gpu_util import assert_close, dev_bf16, image
+from gpu_util import assert_close, dev_bf16, image, prefill_ranges
 from test_gpu_append import CASES
 
 pytestmark = pytest.mark.gpu
@@ -44,6 +44,7 @@ def images(name, seed, scale=1.0):
     gc = kvq.Cache(fmt, B, H, D, N)
     gc.append(dev_bf16(K), dev_bf16(V))
     assert np.array_equal(image(gc), ref.image), "cache images differ"
+    assert prefill_ranges(gc, C, H * G) == 0
     Q = synth.normal_bf16(seed, ("chunk-q",), (B, C, H * G, D))
     O = torch.empty((B, C, H * G, D), dtype=torch.float32, device="cuda")
     ws = torch.full((gc.prefill_workspace_bytes(),), 0xFF, dtype=torch.uint8, device="cuda")

@@ -6,7 +6,8 @@ workspace path (block images, 256-row tiles; 128 at D = 256 for hi + lo keys
 and few tiles).  Each case is checked against the fp64 oracle as in
 test_gpu_prefill (2e-3 + 1e-2 |ref|), with lengths that leave a partial last
 block, rows that leave a partial last tile, fp16 windows and sinks, rotation,
-every code width and mixed widths.
+every code width and mixed widths, and asserts the path and the number of key
+ranges that the dispatch rule gives it.
 """
 import numpy as np
 import pytest
@@ -16,43 +17,53 @@ from test_gpu_prefill import run
 pytestmark = pytest.mark.gpu
 
 NAMES = ["tiny_b16", "affine8", "sink64", "sym4_window", "kivi", "kivi_meta16", "hadamard", "perch_k4v2_window64",
-         "kvarn_sink", "perch8_meta16", "gqa12b", "g256", "had_affine_window", "sym8_window_d256"]
+         "kvarn_sink", "perch8_meta16", "gqa12b", "g256", "had_affine_window", "sym8_window_d256", "had8_d64", "had8_d128",
+         "had8_d256", "had_perch_window"]
 
 
 @pytest.mark.parametrize("name", NAMES)
 def test_fused_key_ranges(name):
-    # 1 unit, 46 rows, 47 blocks: one tile and eleven key ranges, the last block partial
-    run(name, B=1, H=1, G=2, n=1493, C=23, seed=410)
+    # 1 unit, 46 rows, 47 blocks: one tile and eleven key ranges, the last block
+    # partial (8-bit rotating codes at D = 256 do not fit the fused path's LDS)
+    run(name, B=1, H=1, G=2, n=1493, C=23, seed=410, ranges=0 if name == "had8_d256" else 11)
 
 
-@pytest.mark.parametrize("name", ["tiny_b16", "kivi", "gqa12b"])
+@pytest.mark.parametrize("name,n,ranges", [("tiny_b16", 400, (1, 3)), ("kivi", 700, (5, 5)), ("gqa12b", 400, (3, 3))])
 @pytest.mark.parametrize("C", [31, 32, 33, 64, 65])
-def test_fused_tile_edges(name, C):
+def test_fused_tile_edges(name, n, ranges, C):
     # 4 C rows: 124 .. 260 on tiles of 128
-    run(name, B=1, H=2, G=4, n=400 + C, C=C, seed=420 + C)
+    run(name, B=1, H=2, G=4, n=n + C, C=C, seed=420 + C, ranges=ranges[C >= 64])
 
 
 @pytest.mark.parametrize("name", ["tiny_b16", "had_d64_g32"])
-@pytest.mark.parametrize("shape", [dict(B=8, n=1001, C=65), dict(B=36, n=299, C=20)], ids=["ranges", "one_range"])
+@pytest.mark.parametrize("shape", [dict(B=8, n=1001, C=65, ranges=4), dict(B=48, n=299, C=20, ranges=1)],
+                         ids=["ranges", "one_range"])
 def test_fused_two_workgroups_per_cu(name, shape):
     # head size 64: 128 tiles in four key ranges of eight blocks, the last
-    # block partial, and 288 tiles of one range each
+    # block partial, and 384 tiles of one range each
     run(name, H=8, G=2, seed=425, **shape)
 
 
 @pytest.mark.parametrize("name", NAMES)
 def test_workspace_tiles(name):
     # 32 units of 1 + 4 tiles of 256 rows: the workspace path at every head size
-    run(name, B=4, H=8, G=4, n=293, C=260, seed=430)
+    run(name, B=4, H=8, G=4, n=293, C=260, seed=430, ranges=0)
 
 
 @pytest.mark.parametrize("name", ["had_affine_window", "gqa12b"])
 def test_workspace_few_tiles_d256(name):
-    run(name, B=2, H=8, G=4, n=293, C=260, seed=440)
+    run(name, B=2, H=8, G=4, n=293, C=260, seed=440, ranges=0)
 
 
 @pytest.mark.parametrize("name", ["tiny_b16", "kivi", "gqa12b", "hadamard"])
 def test_split_outputs_do_not_depend_on_the_workspace(name):
     # 6 units in one pass, in groups of 4 + 2, and one at a time
-    outs = [run(name, B=3, H=2, G=2, n=1100, C=30, seed=450, ws_units=u) for u in (None, 4, 1)]
+    outs = [run(name, B=3, H=2, G=2, n=1100, C=30, seed=450, ws_units=u, ranges=8) for u in (None, 4, 1)]
     assert np.array_equal(outs[0], outs[1]) and np.array_equal(outs[0], outs[2])
+
+
+@pytest.mark.parametrize("name", ["tiny_b16", "kivi", "hadamard", "gqa12b"])
+def test_fused_calls_repeat_their_bits(name):
+    # the outputs hold the first key range's partial sums until the merge
+    outs = [run(name, B=1, H=2, G=2, n=1100, C=30, seed=455, ranges=8) for _ in range(4)]
+    assert all(np.array_equal(outs[0], o) for o in outs[1:])
