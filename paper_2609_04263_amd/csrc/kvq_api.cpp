@@ -834,6 +834,11 @@ int kvq_internal_prefill_ranges(const kvq_cache* c, int C, int H_q)
     return kvq::prefill_ranges(prefill_params(c, C, H_q, 1.0f), c->D);
 }
 
+int kvq_internal_prefill_tile_rows(const kvq_cache* c, int C, int H_q)
+{
+    return kvq::prefill_tile_rows(prefill_params(c, C, H_q, 1.0f), c->D);
+}
+
 int kvq_internal_project_tile(int M, int N)
 {
     return kvq::project_tile(M, N);

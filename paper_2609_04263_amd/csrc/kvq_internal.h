@@ -199,6 +199,8 @@ size_t prefill_image_bytes(int D);
 // Key ranges per query tile on the fused path of a chunked prefill, 0 for the
 // workspace path.
 int prefill_ranges(const AttnParams& p, int D);
+// Query rows per workgroup on the workspace path.
+int prefill_tile_rows(const AttnParams& p, int D);
 // Chunked prefill over units in groups that fit ws_bytes (at least one unit).
 hipError_t launch_prefill(const AttnParams& p, int D, size_t ws_bytes, hipStream_t stream);
 
@@ -208,3 +210,4 @@ hipError_t launch_prefill(const AttnParams& p, int D, size_t ws_bytes, hipStream
 // Host only; not part of the C ABI.
 extern "C" int kvq_internal_project_tile(int M, int N);
 extern "C" int kvq_internal_prefill_ranges(const kvq_cache* cache, int C, int H_q);
+extern "C" int kvq_internal_prefill_tile_rows(const kvq_cache* cache, int C, int H_q);

@@ -883,6 +883,18 @@ __device__ __forceinline__ Tile make_tile(const AttnParams& p, int unit, int til
 
 constexpr int kNoRow = -(1 << 30);  // position of a query row past the end: every key masked
 
+// Queries are scaled by qscale (returned), sm_scale log2(e) rounded down to a
+// power of two (exact in fp16 below 65504), and the scores take the rest, sscale
+// (qscale keeps the sign of the scale, so sscale > 0; a zero or subnormal scale
+// gives zero queries, zero scores, sscale 1).
+__device__ __forceinline__ float query_scales(const AttnParams& p, float* sscale)
+{
+    const float qscale = __uint_as_float(__float_as_uint(p.sm_log2) & 0xFF800000u);
+    const float rest = qscale == 0.0f ? 1.0f : p.sm_log2 / qscale;
+    *sscale = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(rest)));  // a scalar register
+    return qscale;
+}
+
 // One wave's state: 32 QT query rows (columns of the MFMAs: column l % 32 of
 // tile q is row r0 + 32 (QT wave + q) + l % 32).  KG: key group size / 32 when
 // the format's keys have per-token groups (code blocks then take exact code
@@ -890,6 +902,7 @@ constexpr int kNoRow = -(1 << 30);  // position of a query row past the end: eve
 // exponent per eight tokens.
 template <int D, int KG, int QT, bool ROT>
 struct Wave {
+    static constexpr int kRows = 32 * QT;
     static constexpr int NK = D / 16, NT = D / 32;        // K fragments, 32-channel value tiles
     static constexpr int KS = KG > 0 ? 2 * KG : NK;       // K fragments per group
     static constexpr int NG = NK / KS, NZ = (NG + 1) / 2;  // groups, offset MFMAs per tile
@@ -914,13 +927,7 @@ struct Wave {
         static_assert(QL == 0 || QT == 1, "one query tile per wave");
         ql = spare + 1024 * QL * wave + 16 * lane;
         const int col = lane & 31, hf = lane >> 5;
-        // Queries are scaled by qscale, sm_scale log2(e) rounded down to a
-        // power of two (exact in fp16 below 65504), and the scores take the
-        // rest, sscale (qscale keeps the sign of the scale, so sscale > 0; a
-        // zero or subnormal scale gives zero queries, zero scores, sscale 1)
-        const float qscale = __uint_as_float(__float_as_uint(p.sm_log2) & 0xFF800000u);
-        sscale = qscale == 0.0f ? 1.0f : p.sm_log2 / qscale;
-        sscale = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sscale)));  // a scalar register
+        const float qscale = query_scales(p, &sscale);
         const int first_pos = p.n - p.C, wrow0 = t.r0 + 32 * QT * wave;
         first = __builtin_amdgcn_readfirstlane(wrow0 + 32 * QT <= t.rows ? first_pos + wrow0 / p.G : kNoRow);
 #pragma unroll
@@ -1238,6 +1245,250 @@ struct Wave {
     }
 };
 
+// Wave with 16 query rows at D = 256, on v_mfma_f32_16x16x32_f16 (column l % 16
+// of a wave is one row).  It reads every fragment for half the rows, which
+// makes LDS its limit in long grids, but a tile of eight waves has 128 rows:
+// where tiles of 256 leave CUs idle, or the last ones to run are the longest,
+// twice the tiles are worth more (see small_tiles).
+//
+// Score row 4 (l / 16) + i of key tile kt is token 16 (l / 32) + 4 ((l / 16) & 1)
+// + 8 kt + i, so that a lane's eight scores are the key slots of one 16-byte
+// piece of the image's value fragments.
+template <int KG, bool ROT>
+struct Wave16 {
+    static constexpr int D = 256, kRows = 16;
+    static constexpr int NKS = D / 32, NCT = D / 16;   // K steps, 16-channel value tiles
+    static constexpr int KS = KG > 0 ? KG : NKS, NG = NKS / KS;
+    static_assert(NG <= 4, "one offset product per key tile");
+    half8 q[NKS];
+    float qz;       // lane (col, qg): the query's sum over group qg
+    int qpos;
+    float sscale;   // scores times sscale are exponents (base 2)
+    float bscale;   // ROT: the same for the scores of the present block
+    int first;      // position of the wave's oldest query when all its rows exist
+    floatx4 acc[NCT];
+    floatx4 s[2];   // the scores of the block between scores() and update()
+    float m, lsum;
+
+    static __device__ __forceinline__ int token(int qg) { return 16 * (qg >> 1) + 4 * (qg & 1); }
+
+    __device__ __forceinline__ void init(const AttnParams& p, const Tile& t, uint8_t*, int wave, int lane)
+    {
+        const int col = lane & 15, qg = lane >> 4;
+        const float qscale = query_scales(p, &sscale);
+        const int first_pos = p.n - p.C, wrow0 = t.r0 + kRows * wave, R = wrow0 + col;
+        first = __builtin_amdgcn_readfirstlane(wrow0 + kRows <= t.rows ? first_pos + wrow0 / p.G : kNoRow);
+        const int i = R / p.G, g = R % p.G;
+        const uint16_t* src = p.q + (((size_t)t.b * p.C + i) * p.H_q + (size_t)t.h * p.G + g) * D + 8 * qg;
+        float qsum[NG];
+#pragma unroll
+        for (int j = 0; j < NG; ++j)
+            qsum[j] = 0.0f;
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) {
+            u32x4 w = {0u, 0u, 0u, 0u};
+            if (R < t.rows)
+                w = *(const u32x4*)(src + 32 * ks);
+            const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
+            float v[8], part = 0.0f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                v[e] = __uint_as_float((e & 1) ? (ww[e >> 1] & 0xFFFF0000u) : (ww[e >> 1] << 16)) * qscale;
+                part += v[e];
+            }
+            q[ks] = pack_half8(v);
+            qsum[ks / KS] += part;
+        }
+        qz = 0.0f;
+        if (KG > 0) {
+            // the column's four lanes hold a quarter of every group each
+#pragma unroll
+            for (int j = 0; j < NG; ++j) {
+                float sum = qsum[j] + __shfl_xor(qsum[j], 16);
+                sum += __shfl_xor(sum, 32);
+                qz = qg == j ? sum : qz;
+            }
+        }
+        qpos = R < t.rows ? first_pos + i : kNoRow;
+        m = -INFINITY;
+        lsum = 0.0f;
+#pragma unroll
+        for (int j = 0; j < NCT; ++j)
+            acc[j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+
+    template <typename Hook>
+    __device__ __forceinline__ void scores(const uint8_t* img, bool code, int lane, Hook hook)
+    {
+        const int col = lane & 15, qg = lane >> 4;
+        const int row = token(col >> 2) + (col & 3);  // this lane's K row of tile 0
+        const uint8_t* kb = img + 512 * qg + 16 * row;
+        // step ks, key tile kt of a part: 32 channels of 16 tokens
+        auto frag = [&](int part, int ks, int kt) {
+            return __builtin_bit_cast(half8, *(const u32x4*)(kb + part + 2048 * ks + 128 * kt));
+        };
+        s[0] = s[1] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        if (KG > 0 && code) {
+            const float* ms = (const float*)(img + klo_at<D>());
+            half8 f[2][2];
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt) {
+                f[0][kt] = frag(0, 0, kt);
+                const float za = ms[32 * NG + 32 * min(qg, NG - 1) + 8 * kt + row];
+                s[kt] = __builtin_amdgcn_mfma_f32_16x16x4f32(qg < NG ? za : 0.0f, qz, s[kt], 0, 0, 0);
+            }
+            floatx4 g[2], sc[2];
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) {
+                hook(2 * ks);
+                if (ks % KS == 0) {
+#pragma unroll
+                    for (int kt = 0; kt < 2; ++kt) {
+                        g[kt] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+                        sc[kt] = *(const floatx4*)(ms + 32 * (ks / KS) + 8 * kt + token(qg));
+                    }
+                }
+                if (ks + 1 < NKS) {
+#pragma unroll
+                    for (int kt = 0; kt < 2; ++kt)
+                        f[(ks + 1) & 1][kt] = frag(0, ks + 1, kt);
+                }
+#pragma unroll
+                for (int kt = 0; kt < 2; ++kt)
+                    g[kt] = mfma16(f[ks & 1][kt], q[ks], g[kt]);
+                hook(2 * ks + 1);
+                if (ks % KS == KS - 1) {
+#pragma unroll
+                    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            s[kt][i] = fmaf(sc[kt][i], g[kt][i], s[kt][i]);
+                }
+            }
+        } else {
+            half8 fh[2][2], fl[2][2];
+            uint32_t ef = 0;  // ROT: the octets' exponents, a byte each
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt) {
+                fh[0][kt] = frag(0, 0, kt);
+                fl[0][kt] = frag(klo_at<D>(), 0, kt);
+            }
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) {
+                hook(2 * ks);
+                if (ks + 1 < NKS) {
+#pragma unroll
+                    for (int kt = 0; kt < 2; ++kt) {
+                        fh[(ks + 1) & 1][kt] = frag(0, ks + 1, kt);
+                        fl[(ks + 1) & 1][kt] = frag(klo_at<D>(), ks + 1, kt);
+                    }
+                }
+                if constexpr (ROT) {
+                    if (ks == NKS / 2) {
+                        // channel D / 2 (octet_exponent): lanes 0 .. 7 hold octet kt,
+                        // lanes 8 .. 15 octet 2 + kt
+#pragma unroll
+                        for (int kt = 0; kt < 2; ++kt) {
+                            u32x4 w = __builtin_bit_cast(u32x4, fl[ks & 1][kt]);
+                            const uint32_t b = (uint32_t)__ballot((w.x & kExponentBit) != 0);
+                            ef |= ((b & 0xFFu) | (b << 8 & 0xFF0000u)) << (8 * kt);
+                            w.x &= ~kExponentBit;
+                            fl[ks & 1][kt] = __builtin_bit_cast(half8, w);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int kt = 0; kt < 2; ++kt) {
+                    s[kt] = mfma16(fh[ks & 1][kt], q[ks], s[kt]);
+                    s[kt] = mfma16(fl[ks & 1][kt], q[ks], s[kt]);
+                }
+                hook(2 * ks + 1);
+            }
+            if constexpr (ROT) {
+                int top = (int)(ef & 0xFFu);
+                if (ef != (uint32_t)top * 0x01010101u) {
+#pragma unroll
+                    for (int j = 1; j < 4; ++j)
+                        top = max(top, (int)(ef >> (8 * j) & 0xFFu));
+#pragma unroll
+                    for (int kt = 0; kt < 2; ++kt) {
+                        const int e = (int)(ef >> (16 * (qg >> 1) + 8 * kt) & 0xFFu);
+                        s[kt] *= __uint_as_float((uint32_t)max(127 + e - top, 0) << 23);
+                    }
+                }
+                bscale = __uint_as_float(__float_as_uint(sscale) + ((uint32_t)(top - kExponentBias) << 23));
+            }
+        }
+    }
+
+    __device__ __forceinline__ void update(const uint8_t* img, int blk, int lane)
+    {
+        const int col = lane & 15, qg = lane >> 4;
+        const uint8_t* vb = img + vt_at<D>() + 512 * qg + 16 * col;
+        auto vfrag = [&](int c) { return __builtin_bit_cast(half8, *(const u32x4*)(vb + 2048 * (c >> 1) + 256 * (c & 1))); };
+        constexpr int PF = 3;
+        half8 vf[PF];
+#pragma unroll
+        for (int c = 0; c < PF; ++c)
+            vf[c] = vfrag(c);
+        const float scale = ROT ? bscale : sscale;
+        if (!(32 * blk + 31 <= first)) {
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    s[kt][i] = 32 * blk + 8 * kt + token(qg) + i <= qpos ? s[kt][i] : -INFINITY;
+        }
+        float lm = s[0][0];
+#pragma unroll
+        for (int e = 1; e < 8; ++e)
+            lm = fmaxf(lm, s[e >> 2][e & 3]);
+        lm *= scale;
+        // (the running maximum as in Wave::update)
+        if (__any(lm > m + 8.0f)) {
+            float bm = fmaxf(lm, __shfl_xor(lm, 16));
+            bm = fmaxf(bm, __shfl_xor(bm, 32));
+            if (bm > m + 8.0f) {
+                const float alpha = m == -INFINITY ? 0.0f : fast_exp2(m - bm);
+                m = bm;
+                lsum *= alpha;
+#pragma unroll
+                for (int c = 0; c < NCT; ++c)
+                    acc[c] *= alpha;
+            }
+        }
+        const float mn = m == -INFINITY ? 0.0f : m;
+        float pv[8], ps = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            pv[e] = fast_exp2(fmaf(s[e >> 2][e & 3], scale, -mn));
+            ps += pv[e];
+        }
+        lsum += ps;
+        const half8 ph = pack_half8(pv);
+#pragma unroll
+        for (int c = 0; c < NCT; ++c) {
+            acc[c] = mfma16(vf[c % PF], ph, acc[c]);
+            if (c + PF < NCT)
+                vf[c % PF] = vfrag(c + PF);
+        }
+    }
+
+    __device__ __forceinline__ void finish(const AttnParams& p, const Tile& t, int, int wave, int lane)
+    {
+        const int col = lane & 15, qg = lane >> 4, R = t.r0 + kRows * wave + col;
+        float l = lsum + __shfl_xor(lsum, 16);
+        l += __shfl_xor(l, 32);
+        if (R >= t.rows)
+            return;
+        const float mul = l > 0.0f ? 1.0f / l : 0.0f;
+        float* dst = p.out + (((size_t)t.b * p.C + R / p.G) * p.H_q + (size_t)t.h * p.G + R % p.G) * D;
+#pragma unroll
+        for (int c = 0; c < NCT; ++c)
+            *(floatx4*)(dst + 16 * c + 4 * qg) = acc[c] * mul;
+    }
+};
+
 // Workgroup w runs on XCD w mod 8: the contiguous range of work items an XCD
 // takes shares a unit's blocks in its L2.
 __device__ __forceinline__ int xcd_item()
@@ -1246,11 +1497,11 @@ __device__ __forceinline__ int xcd_item()
     return (W & 7) == 0 ? (blockIdx.x & 7) * (W >> 3) + (blockIdx.x >> 3) : blockIdx.x;
 }
 
-// NW waves per workgroup, 32 QT NW query rows per tile.
-template <int D, int KG, int NW, bool ROT>
-__global__ __launch_bounds__(64 * NW, D == 256 && NW == 4 ? 1 : 2) void attn_kernel(AttnParams p)
+// W: a wave's state and rows; W::kRows waves<D>() query rows per tile.
+template <int D, typename W>
+__global__ __launch_bounds__(64 * waves<D>(), 2) void attn_kernel(AttnParams p)
 {
-    constexpr int QT = qtiles<D>();
+    constexpr int NW = waves<D>();
     constexpr int BI = image_bytes<D>(), NST = stages<D>();
     constexpr int CW = BI / 1024 / NW;  // 1 KiB copies of an image per wave
     static_assert(CW * 1024 * NW == BI && CW <= D / 16, "whole copies, one beside a K fragment");
@@ -1260,8 +1511,8 @@ __global__ __launch_bounds__(64 * NW, D == 256 && NW == 4 ? 1 : 2) void attn_ker
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // the longest (newest) tiles of a unit start first
     const int L = xcd_item(), uloc = __builtin_amdgcn_readfirstlane(L / p.pf_tiles);
-    const Tile t = make_tile(p, p.pf_u0 + uloc, p.pf_tiles - 1 - (L - uloc * p.pf_tiles), 32 * QT * NW);
-    Wave<D, KG, QT, ROT> w;
+    const Tile t = make_tile(p, p.pf_u0 + uloc, p.pf_tiles - 1 - (L - uloc * p.pf_tiles), W::kRows * NW);
+    W w;
     w.init(p, t, plds + NST * BI, wave, lane);
 
     const uint32_t lbase = (uint32_t)(uintptr_t)plds;
@@ -1494,16 +1745,29 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(AttnParams p)
 
 typedef void (*Kernel)(AttnParams);
 
+template <int D, int KG, bool ROT = false>
+constexpr Kernel attn_of = attn_kernel<D, Wave<D, KG, qtiles<D>(), ROT>>;
+
 template <int D>
 Kernel pick(int kg, bool rot)
 {
-    constexpr int NW = waves<D>();
-    return rot       ? attn_kernel<D, 0, NW, true>
-           : kg == 1 ? attn_kernel<D, (D >= 256 ? 0 : 1), NW, false>
-           : kg == 2 ? attn_kernel<D, 2, NW, false>
-           : kg == 4 ? attn_kernel<D, (D >= 128 ? 4 : 1), NW, false>
-           : kg == 8 ? attn_kernel<D, (D >= 256 ? 8 : 1), NW, false>
-                     : attn_kernel<D, 0, NW, false>;
+    return rot       ? attn_of<D, 0, true>
+           : kg == 1 ? attn_of<D, (D >= 256 ? 0 : 1)>
+           : kg == 2 ? attn_of<D, 2>
+           : kg == 4 ? attn_of<D, (D >= 128 ? 4 : 1)>
+           : kg == 8 ? attn_of<D, (D >= 256 ? 8 : 1)>
+                     : attn_of<D, 0>;
+}
+
+template <int D>
+Kernel pick16(int kg, bool rot)
+{
+    static_assert(D == 256);
+    return rot       ? attn_kernel<D, Wave16<0, true>>
+           : kg == 2 ? attn_kernel<D, Wave16<2, false>>
+           : kg == 4 ? attn_kernel<D, Wave16<4, false>>
+           : kg == 8 ? attn_kernel<D, Wave16<8, false>>
+                     : attn_kernel<D, Wave16<0, false>>;
 }
 
 // Key ranges per query tile on the fused path, or 0 for the workspace path.
@@ -1552,6 +1816,35 @@ int fused_splits(const AttnParams& p)
         S = cost(two) < cost(S) ? two : S;
     }
     return cost(S) < image ? (int)S : 0;
+}
+
+// Whether the workspace path at D = 256 takes tiles of 128 query rows (Wave16)
+// instead of 256.  A block takes the smaller tile 0.7 times as long (0.8 with hi
+// + lo keys, measured with both filling the CUs once), so it wins where tiles
+// of 256 rows do not cover the CUs, or finish unevenly.  estimate: blocks the
+// last CU computes; tiles start unit by unit, a unit's longest first, so that the
+// last unit's longest may start when the first short tiles end.  Measured, 256 /
+// 128 rows (groups of 64, 8 heads of two query heads): 2048 tokens at B = 1
+// 137 / 103 us, B = 2 145 / 121, B = 3 188 / 203; 2048 of 8192 at B = 1 450 /
+// 331, B = 3 937 / 930; hi + lo keys, 2048 tokens at B = 1 148 / 118, B = 2
+// 158 / 141; rotated 145 / 119.
+template <int D>
+bool small_tiles(const AttnParams& p)
+{
+    static_assert(D == 256);
+    const long long units = (long long)p.B * p.H, rows = (long long)p.C * p.G;
+    const double nb = p.pf_nvb;
+    const auto estimate = [&](int per) {
+        const double n = (double)(units * ((rows + per - 1) / per));
+        if (n <= 256)
+            return nb;
+        const double tok = (double)per / p.G, shortest = nb - (p.C > tok ? p.C - tok : 0.0) / 32;
+        const double even = n * (nb + shortest) / 2 / 256, rounds = (double)(((long long)n + 255) / 256) * nb;
+        const double uneven = shortest + (even > nb ? even : nb);
+        return uneven < rounds ? uneven : rounds;
+    };
+    const bool hilo = p.rotate || p.k_axis != KVQ_PER_TOKEN || p.k_group == 32;
+    return (hilo ? 0.8 : 0.7) * estimate(kRows / 2) < estimate(kRows);
 }
 
 template <int D, int KG, bool W8, bool ROT>
@@ -1619,16 +1912,11 @@ hipError_t launch(const AttnParams& p0, size_t ws_bytes, hipStream_t stream)
     void (*deq)(AttnParams) = w8 ? (rot ? dequant_kernel<D, true, true> : dequant_kernel<D, true, false>)
                                  : (rot ? dequant_kernel<D, false, true> : dequant_kernel<D, false, false>);
     Kernel att = pick<D>(kg, rot);
-    int nw = waves<D>(), per = kRows;
+    int per = kRows;
     if constexpr (D == 256) {
-        // hi + lo keys at D = 256 are bound by LDS reads (48 KiB per wave and
-        // block), which half the waves halve: where tiles of 256 rows do not
-        // cover the CUs, four waves of 128 rows (measured at 64 such tiles:
-        // 265 -> 232 us; with code blocks no gain)
-        if ((rot || kg <= 1) && units * ((rows + kRows - 1) / kRows) <= 128) {
-            att = rot ? attn_kernel<D, 0, 4, true> : attn_kernel<D, 0, 4, false>;
-            nw = 4;
-            per = 128;
+        if (small_tiles<D>(p0)) {
+            att = pick16<D>(kg, rot);
+            per = kRows / 2;
         }
     }
     const int tiles = (rows + per - 1) / per;
@@ -1639,7 +1927,7 @@ hipError_t launch(const AttnParams& p0, size_t ws_bytes, hipStream_t stream)
         p.S_tot = 1;
         const int nu = units - u0 < group ? units - u0 : group;
         launch_kernel(deq, dim3(p.pf_nvb, nu), dim3(kDqThreads), rot ? scratch_bytes<D>() : 0, stream, p);
-        launch_kernel(att, dim3(tiles * nu), dim3(64 * nw), attn_lds_bytes<D>(), stream, p);
+        launch_kernel(att, dim3(tiles * nu), dim3(64 * waves<D>()), attn_lds_bytes<D>(), stream, p);
     }
     return hipGetLastError();
 }
@@ -1654,6 +1942,7 @@ hipError_t launch_prefill_256(const AttnParams& p, size_t ws_bytes, hipStream_t 
 int prefill_ranges_64(const AttnParams& p);
 int prefill_ranges_128(const AttnParams& p);
 int prefill_ranges_256(const AttnParams& p);
+int prefill_tile_rows_256(const AttnParams& p);
 
 #if KVQ_PREFILL_D == 64
 hipError_t launch_prefill_64(const AttnParams& p, size_t ws_bytes, hipStream_t stream)
@@ -1669,6 +1958,11 @@ int prefill_ranges_64(const AttnParams& p)
 int prefill_ranges(const AttnParams& p, int D)
 {
     return D == 64 ? prefill_ranges_64(p) : D == 128 ? prefill_ranges_128(p) : prefill_ranges_256(p);
+}
+
+int prefill_tile_rows(const AttnParams& p, int D)
+{
+    return D == 256 ? prefill_tile_rows_256(p) : pre::kRows;
 }
 
 size_t prefill_image_bytes(int D)
@@ -1708,6 +2002,11 @@ hipError_t launch_prefill_256(const AttnParams& p, size_t ws_bytes, hipStream_t 
 int prefill_ranges_256(const AttnParams& p)
 {
     return pre::fused_splits<256>(p);
+}
+
+int prefill_tile_rows_256(const AttnParams& p)
+{
+    return pre::small_tiles<256>(p) ? pre::kRows / 2 : pre::kRows;
 }
 #endif
 

@@ -48,3 +48,9 @@ def prefill_ranges(cache, C: int, H_q: int) -> int:
     """Key ranges of a chunked prefill's fused path, 0 for the workspace path."""
     from paper_2609_04263_amd import kvq
     return kvq._lib.kvq_internal_prefill_ranges(cache.handle, C, H_q)
+
+
+def prefill_tile_rows(cache, C: int, H_q: int) -> int:
+    """Query rows per workgroup of a chunked prefill's workspace path."""
+    from paper_2609_04263_amd import kvq
+    return kvq._lib.kvq_internal_prefill_tile_rows(cache.handle, C, H_q)

@@ -20,7 +20,7 @@ import torch
 import oracle
 from paper_2609_04263_amd import configs, synth
 
-from gpu_util import assert_close, dev_bf16, image, prefill_ranges
+from gpu_util import assert_close, dev_bf16, image, prefill_ranges, prefill_tile_rows
 from test_gpu_append import CASES
 
 pytestmark = pytest.mark.gpu
@@ -30,6 +30,10 @@ pytestmark = pytest.mark.gpu
 EXTRA = {
     "had_d64_g32": (configs.make_format(4, 4, k_group=32, v_group=32, rotate=64), 64),
     "had_d128_g32": (configs.make_format(4, 2, k_mode=1, v_mode=1, k_group=32, v_group=32, rotate=128), 128),
+    # eight key groups per token, and per-channel keys, at the largest head size
+    "affine_g32_d256": (configs.make_format(4, 4, k_group=32, v_group=32), 256),
+    "affine_g128_d256": (configs.make_format(4, 4, k_group=128, v_group=64), 256),
+    "perch_d256": (configs.make_format(2, 2, k_axis=1, k_group=32, v_group=32, residual=32, flush=32), 256),
     # 8-bit codes, and per-channel keys, of rotating formats
     "had8_d64": (configs.make_format(8, 8, k_group=32, v_group=32, rotate=64), 64),
     "had8_d128": (configs.make_format(8, 8, k_group=64, v_group=64, rotate=128), 128),
@@ -39,8 +43,9 @@ EXTRA = {
 }
 
 
-def run(name, B, H, G, n, C, seed, sm=None, ws_units=None, ranges=None):
-    # ranges: the key ranges that the call is meant to take (0: the workspace path)
+def run(name, B, H, G, n, C, seed, sm=None, ws_units=None, ranges=None, tile_rows=None):
+    # ranges: the key ranges that the call is meant to take (0: the workspace
+    # path); tile_rows: the query rows per workgroup there
     from paper_2609_04263_amd import kvq
     fmt, D = CASES[name] if name in CASES else EXTRA[name]
     outlier = ("student_t", 3.0) if fmt["rotate"] else ("scale", 4, 20.0)
@@ -56,6 +61,8 @@ def run(name, B, H, G, n, C, seed, sm=None, ws_units=None, ranges=None):
     H_q = H * G
     if ranges is not None:
         assert prefill_ranges(gc, C, H_q) == ranges
+    if tile_rows is not None:
+        assert prefill_tile_rows(gc, C, H_q) == tile_rows
     Q = synth.normal_bf16(seed, ("chunk-q",), (B, C, H_q, D))
     sm = 1.0 / np.sqrt(D) if sm is None else sm
     O = torch.full((B, C, H_q, D), float("nan"), dtype=torch.float32, device="cuda")

@@ -2,8 +2,8 @@
 
 Few query rows take the fused path (packed blocks reconstructed in LDS, the
 key range split over workgroups when there are few query tiles), many rows the
-workspace path (block images, 256-row tiles; 128 at D = 256 for hi + lo keys
-and few tiles).  Each case is checked against the fp64 oracle as in
+workspace path (block images, 256-row tiles; 128 at D = 256 where tiles are
+few).  Each case is checked against the fp64 oracle as in
 test_gpu_prefill (2e-3 + 1e-2 |ref|), with lengths that leave a partial last
 block, rows that leave a partial last tile, fp16 windows and sinks, rotation,
 every code width and mixed widths, and asserts the path and the number of key
@@ -50,9 +50,20 @@ def test_workspace_tiles(name):
     run(name, B=4, H=8, G=4, n=293, C=260, seed=430, ranges=0)
 
 
-@pytest.mark.parametrize("name", ["had_affine_window", "gqa12b"])
+D256 = ["gqa12b", "g256", "affine_g128_d256", "affine_g32_d256", "perch_d256", "had_affine_window", "sym8_window_d256",
+        "had8_d256"]
+
+
+@pytest.mark.parametrize("name", D256)
 def test_workspace_few_tiles_d256(name):
-    run(name, B=2, H=8, G=4, n=293, C=260, seed=440, ranges=0)
+    # 1040 rows per unit: nine tiles of 128, the last partial
+    run(name, B=2, H=8, G=4, n=293, C=260, seed=440, ranges=0, tile_rows=128)
+
+
+@pytest.mark.parametrize("name", D256)
+def test_workspace_many_tiles_d256(name):
+    # 320 rows per unit: 240 tiles of 256, half of them partial
+    run(name, B=8, H=15, G=8, n=293, C=40, seed=445, ranges=0, tile_rows=256)
 
 
 @pytest.mark.parametrize("name", ["tiny_b16", "kivi", "gqa12b", "hadamard"])
