@@ -112,43 +112,40 @@ struct RowStage {
         }
     }
 
-    // The values are widened to fp32; for tokens of this call rotated, and
-    // rounded to fp16 when a window exists.
-    // The eight values of step k as the coder sees them.
+    // The eight values of step k as the coder sees them: widened to fp32; for
+    // tokens of this call rotated, and rounded to fp16 when a window exists.
     __device__ __forceinline__ void widen(const AppendParams& p, int tb, int k, float* v) const
     {
-        {
-            const int t = tb + row(k);
-            const bool fresh = !(t >= p.q0 && t < p.q1) || t >= p.n0;  // bf16 (zero rows: zero words)
-            const uint32_t ww[4] = {w[k].x, w[k].y, w[k].z, w[k].w};
+        const int t = tb + row(k);
+        const bool fresh = !(t >= p.q0 && t < p.q1) || t >= p.n0;  // bf16 (zero rows: zero words)
+        const uint32_t ww[4] = {w[k].x, w[k].y, w[k].z, w[k].w};
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if (fresh) {
-                    v[2 * q] = __uint_as_float(ww[q] << 16);
-                    v[2 * q + 1] = __uint_as_float(ww[q] & 0xFFFF0000u);
-                } else {
-                    v[2 * q] = f16_bits_to_f32((uint16_t)ww[q]);
-                    v[2 * q + 1] = f16_bits_to_f32((uint16_t)(ww[q] >> 16));
-                }
+        for (int q = 0; q < 4; ++q) {
+            if (fresh) {
+                v[2 * q] = __uint_as_float(ww[q] << 16);
+                v[2 * q + 1] = __uint_as_float(ww[q] & 0xFFFF0000u);
+            } else {
+                v[2 * q] = f16_bits_to_f32((uint16_t)ww[q]);
+                v[2 * q + 1] = f16_bits_to_f32((uint16_t)(ww[q] >> 16));
             }
-            const bool input = t >= p.q0 && t < p.q1 && t >= p.n0;
-            if (p.rotate) {
-                float r[8];
+        }
+        const bool input = t >= p.q0 && t < p.q1 && t >= p.n0;
+        if (p.rotate) {
+            float r[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                r[e] = v[e];
+            rotate8<D>(r, chan(k) >> 3, p.rot_c);
+            if (input) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
-                    r[e] = v[e];
-                rotate8<D>(r, chan(k) >> 3, p.rot_c);
-                if (input) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        v[e] = r[e];
-                }
+                    v[e] = r[e];
             }
-            if (p.ring && input) {
+        }
+        if (p.ring && input) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    v[e] = f16_bits_to_f32(f32_to_f16_bits(v[e]));
-            }
+            for (int e = 0; e < 8; ++e)
+                v[e] = f16_bits_to_f32(f32_to_f16_bits(v[e]));
         }
     }
 };

@@ -60,36 +60,27 @@ __device__ __forceinline__ int proj_of(const ProjParams& p, int n)
     return n < p.n1 ? 0 : (n < p.n2 ? 1 : 2);
 }
 
-__device__ __forceinline__ void store_out(const ProjParams& p, int m, int n, float v)
+// Element (m, n) of the activation pass's fp32 sums v, scaled, into the workspace.
+__device__ __forceinline__ void store_activation(const ProjParams& p, int m, int n, float v)
 {
     if (m >= p.M || n >= p.N)
         return;
-    if (p.yf) {
-        const float t = v * p.scale;
-        if (p.t_hilo) {
-            // bf16 hi (nearest) and lo (remainder, nearest) of the scaled
-            // activation (split_bf16x8's operands, precomputed), [M][3][2 r]:
-            // in projection n / r's segment, rank column j's hi at
-            // 32 (j / 16) + j % 16 and its lo 16 further, so that K stages
-            // of 32 meet hi then lo of each 16 columns, the order in which
-            // the K-extension after the main loop adds them
-            const int r = p.N / 3, pj = n / r, j = n - pj * r;
-            uint16_t* row = (uint16_t*)p.yf + (size_t)m * 2 * p.N + (size_t)pj * 2 * r + 32 * (j >> 4) + (j & 15);
-            const uint16_t hi = f32_to_bf16(t);
-            row[0] = hi;
-            row[16] = f32_to_bf16(t - bf16_to_f32(hi));
-        } else {
-            p.yf[(size_t)m * p.N + n] = t;
-        }
-        return;
+    const float t = v * p.scale;
+    if (p.t_hilo) {
+        // bf16 hi (nearest) and lo (remainder, nearest) of the scaled
+        // activation (split_bf16x8's operands, precomputed), [M][3][2 r]:
+        // in projection n / r's segment, rank column j's hi at
+        // 32 (j / 16) + j % 16 and its lo 16 further, so that K stages
+        // of 32 meet hi then lo of each 16 columns, the order in which
+        // the K-extension after the main loop adds them
+        const int r = p.N / 3, pj = n / r, j = n - pj * r;
+        uint16_t* row = (uint16_t*)p.yf + (size_t)m * 2 * p.N + (size_t)pj * 2 * r + 32 * (j >> 4) + (j & 15);
+        const uint16_t hi = f32_to_bf16(t);
+        row[0] = hi;
+        row[16] = f32_to_bf16(t - bf16_to_f32(hi));
+    } else {
+        p.yf[(size_t)m * p.N + n] = t;
     }
-    uint16_t o = f32_to_bf16(v);
-    if (n < p.n1)
-        p.y0[(size_t)m * p.n1 + n] = o;
-    else if (n < p.n2)
-        p.y1[(size_t)m * (p.n2 - p.n1) + (n - p.n1)] = o;
-    else
-        p.y2[(size_t)m * (p.N - p.n2) + (n - p.n2)] = o;
 }
 
 // Adapter operand of weight row n for the 32-wide chunk kk of the rank
@@ -670,7 +661,7 @@ __global__ __launch_bounds__(kThreads) void proj_big_kernel(ProjParams p)
         for (int ni = 0; ni < 4; ++ni)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                store_out(p, m0 + wm * 16 * MI + 16 * mi + 4 * qg + i, n0 + wn * 64 + 16 * ni + r, acc[mi][ni][i]);
+                store_activation(p, m0 + wm * 16 * MI + 16 * mi + 4 * qg + i, n0 + wn * 64 + 16 * ni + r, acc[mi][ni][i]);
 }
 
 
@@ -1632,7 +1623,7 @@ __global__ __launch_bounds__(64 * kActWaves, 2) void proj_act_kernel(ProjParams 
         for (int j = 0; j < NT; ++j)
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                store_out(p, m0 + 16 * i + 4 * qg + e, n0 + 16 * j + r, acc[i][j][e]);
+                store_activation(p, m0 + 16 * i + 4 * qg + e, n0 + 16 * j + r, acc[i][j][e]);
 }
 
 // XCDs of the current device (1 when unknown), cached per device.
@@ -1688,7 +1679,7 @@ int project_tile(int M, int N)
 
 bool project_adapter_stages(int M, int d_in, int d_q, int d_kv, int rank)
 {
-    return project_tile(M, d_q + 2 * d_kv) < 0 && rank > 0 && rank % 16 == 0 && M >= kGM && d_q + 2 * d_kv >= kGN && d_in % kGK == 0 && d_q % kGN == 0 &&
+    return project_tile(M, d_q + 2 * d_kv) < 0 && rank > 0 && rank % 16 == 0 && d_in % kGK == 0 && d_q % kGN == 0 &&
            d_kv % kGN == 0;
 }
 
