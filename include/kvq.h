@@ -284,7 +284,9 @@ kvq_status kvq_decode_attn_noalloc(const kvq_cache* cache, const void* Q, int H_
  *   O  fp32 [B][C][H_q][D], normalized
  * Reconstructed keys and values (after rotation, for a rotating format)
  * enter the products as binary16 MFMA operands, so their magnitudes must
- * stay below 65504 (binary16's largest finite value).
+ * stay below 65504 (binary16's largest finite value).  Coded keys of
+ * per-token groups are exempt: they enter as exact codes or scaled by powers
+ * of two (except, without rotation, groups of 32 at D = 256).
  * H_q a multiple of H_kv.  Pointers 16-byte aligned device memory owned by
  * the caller; invalid arguments return KVQ_ERR_ARG before any launch.
  *   workspace  device scratch for the reconstructed blocks of each (b, h):

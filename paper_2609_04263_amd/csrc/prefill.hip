@@ -43,11 +43,12 @@
 // Why 32 rows per wave: a wave reads every K and V fragment of a block from
 // LDS once for all of its rows.  With 16 rows at D = 256 the eight waves read
 // 256 KiB per block against 1024 cycles of MFMA work, and LDS, not the matrix
-// cores, was the limit (3500 cycles per block of 128 rows; now 4070 per block
-// of 256, 2320 of them MFMA); 32 rows halve that, and take 128 accumulator and
+// cores, was the limit (3500 cycles per block of 128 rows; now 4385 per block
+// of 256, 2300 of them MFMA); 32 rows halve that, and take 128 accumulator and
 // 64 query registers, which fits two waves per SIMD only because fragment
 // order needs no address arithmetic.  A chunk of 2048 tokens at the end of
-// 8192 (B = 8, 16 query heads on 8, D = 256): 2570 -> 2170 us per call.
+// 8192 (B = 8, 16 query heads on 8, D = 256): 2590 -> 2160 to 2280 us per call.
+// Few tiles at D = 256 keep 16 rows per wave (Wave16).
 // Sink tokens (fp16 rows) come first as blocks of their own; fp16 window
 // tokens past the coded ones are read from the ring.
 
