@@ -1252,9 +1252,11 @@ struct Wave {
 // where tiles of 256 leave CUs idle, or the last ones to run are the longest,
 // twice the tiles are worth more (see small_tiles).
 //
-// Score row 4 (l / 16) + i of key tile kt is token 16 (l / 32) + 4 ((l / 16) & 1)
-// + 8 kt + i, so that a lane's eight scores are the key slots of one 16-byte
-// piece of the image's value fragments.
+// Score row 4 (l / 16) + i of key tile kt is token 16 u + 4 ((l / 16) & 1) + 8 (kt
+// ^ u) + i, u = l / 32: a lane's eight scores are the key slots of one 16-byte
+// piece of the image's value fragments (its halves swapped where u = 1), and the
+// 16 rows of a K read lie in distinct banks (with kt for kt ^ u they met in half
+// of them).
 template <int KG, bool ROT>
 struct Wave16 {
     static constexpr int D = 256, kRows = 16;
@@ -1271,7 +1273,7 @@ struct Wave16 {
     floatx4 s[2];   // the scores of the block between scores() and update()
     float m, lsum;
 
-    static __device__ __forceinline__ int token(int qg) { return 16 * (qg >> 1) + 4 * (qg & 1); }
+    static __device__ __forceinline__ int token(int qg, int kt) { return 16 * (qg >> 1) + 4 * (qg & 1) + 8 * (kt ^ (qg >> 1)); }
 
     __device__ __forceinline__ void init(const AttnParams& p, const Tile& t, uint8_t*, int wave, int lane)
     {
@@ -1322,11 +1324,11 @@ struct Wave16 {
     __device__ __forceinline__ void scores(const uint8_t* img, bool code, int lane, Hook hook)
     {
         const int col = lane & 15, qg = lane >> 4;
-        const int row = token(col >> 2) + (col & 3);  // this lane's K row of tile 0
-        const uint8_t* kb = img + 512 * qg + 16 * row;
+        const int row[2] = {token(col >> 2, 0) + (col & 3), token(col >> 2, 1) + (col & 3)};  // this lane's K rows
+        const uint8_t* kb[2] = {img + 512 * qg + 16 * row[0], img + 512 * qg + 16 * row[1]};
         // step ks, key tile kt of a part: 32 channels of 16 tokens
         auto frag = [&](int part, int ks, int kt) {
-            return __builtin_bit_cast(half8, *(const u32x4*)(kb + part + 2048 * ks + 128 * kt));
+            return __builtin_bit_cast(half8, *(const u32x4*)(kb[kt] + part + 2048 * ks));
         };
         s[0] = s[1] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
         if (KG > 0 && code) {
@@ -1335,7 +1337,7 @@ struct Wave16 {
 #pragma unroll
             for (int kt = 0; kt < 2; ++kt) {
                 f[0][kt] = frag(0, 0, kt);
-                const float za = ms[32 * NG + 32 * min(qg, NG - 1) + 8 * kt + row];
+                const float za = ms[32 * NG + 32 * min(qg, NG - 1) + row[kt]];
                 s[kt] = __builtin_amdgcn_mfma_f32_16x16x4f32(qg < NG ? za : 0.0f, qz, s[kt], 0, 0, 0);
             }
             floatx4 g[2], sc[2];
@@ -1346,7 +1348,7 @@ struct Wave16 {
 #pragma unroll
                     for (int kt = 0; kt < 2; ++kt) {
                         g[kt] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-                        sc[kt] = *(const floatx4*)(ms + 32 * (ks / KS) + 8 * kt + token(qg));
+                        sc[kt] = *(const floatx4*)(ms + 32 * (ks / KS) + token(qg, kt));
                     }
                 }
                 if (ks + 1 < NKS) {
@@ -1387,12 +1389,12 @@ struct Wave16 {
                 if constexpr (ROT) {
                     if (ks == NKS / 2) {
                         // channel D / 2 (octet_exponent): lanes 0 .. 7 hold octet kt,
-                        // lanes 8 .. 15 octet 2 + kt
+                        // lanes 8 .. 15 octet 3 - kt
 #pragma unroll
                         for (int kt = 0; kt < 2; ++kt) {
                             u32x4 w = __builtin_bit_cast(u32x4, fl[ks & 1][kt]);
                             const uint32_t b = (uint32_t)__ballot((w.x & kExponentBit) != 0);
-                            ef |= ((b & 0xFFu) | (b << 8 & 0xFF0000u)) << (8 * kt);
+                            ef |= (b & 0xFFu) << (8 * kt) | (b >> 8 & 0xFFu) << (24 - 8 * kt);
                             w.x &= ~kExponentBit;
                             fl[ks & 1][kt] = __builtin_bit_cast(half8, w);
                         }
@@ -1413,7 +1415,7 @@ struct Wave16 {
                         top = max(top, (int)(ef >> (8 * j) & 0xFFu));
 #pragma unroll
                     for (int kt = 0; kt < 2; ++kt) {
-                        const int e = (int)(ef >> (16 * (qg >> 1) + 8 * kt) & 0xFFu);
+                        const int e = (int)(ef >> (token(qg, kt) & 24) & 0xFFu);  // octet token / 8
                         s[kt] *= __uint_as_float((uint32_t)max(127 + e - top, 0) << 23);
                     }
                 }
@@ -1438,7 +1440,7 @@ struct Wave16 {
             for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    s[kt][i] = 32 * blk + 8 * kt + token(qg) + i <= qpos ? s[kt][i] : -INFINITY;
+                    s[kt][i] = 32 * blk + token(qg, kt) + i <= qpos ? s[kt][i] : -INFINITY;
         }
         float lm = s[0][0];
 #pragma unroll
@@ -1466,7 +1468,8 @@ struct Wave16 {
             ps += pv[e];
         }
         lsum += ps;
-        const half8 ph = pack_half8(pv);
+        const u32x4 pw = __builtin_bit_cast(u32x4, pack_half8(pv));
+        const half8 ph = __builtin_bit_cast(half8, qg < 2 ? pw : u32x4{pw.z, pw.w, pw.x, pw.y});
 #pragma unroll
         for (int c = 0; c < NCT; ++c) {
             acc[c] = mfma16(vf[c % PF], ph, acc[c]);
@@ -1820,15 +1823,14 @@ int fused_splits(const AttnParams& p)
 }
 
 // Whether the workspace path at D = 256 takes tiles of 128 query rows (Wave16)
-// instead of 256.  A block takes the smaller tile 0.7 times as long (0.8 with hi
-// + lo keys, measured with both filling the CUs once), so it wins where tiles
-// of 256 rows do not cover the CUs, or finish unevenly.  estimate: blocks the
-// last CU computes; tiles start unit by unit, a unit's longest first, so that the
-// last unit's longest may start when the first short tiles end.  Measured, 256 /
-// 128 rows (groups of 64, 8 heads of two query heads): 2048 tokens at B = 1
-// 137 / 103 us, B = 2 145 / 121, B = 3 188 / 203; 2048 of 8192 at B = 1 450 /
-// 331, B = 3 937 / 930; hi + lo keys, 2048 tokens at B = 1 148 / 118, B = 2
-// 158 / 141; rotated 145 / 119.
+// instead of 256.  A block takes the smaller tile 0.7 times as long (measured with
+// both filling the CUs once), so it wins where tiles of 256 rows do not cover the
+// CUs, or finish unevenly.  estimate: blocks the last CU computes; tiles start
+// unit by unit, a unit's longest first, so that the last unit's longest may start
+// when the first short tiles end.  Measured, 256 / 128 rows (groups of 64, 8 heads
+// of two query heads): 2048 tokens at B = 1 137 / 100 us, B = 2 145 / 121, B = 3
+// 188 / 203; 2048 of 8192 at B = 1 450 / 321, B = 3 937 / 930; hi + lo keys, 2048
+// tokens at B = 1 148 / 103, B = 2 158 / 130; rotated, B = 1 145 / 104.
 template <int D>
 bool small_tiles(const AttnParams& p)
 {
@@ -1844,8 +1846,7 @@ bool small_tiles(const AttnParams& p)
         const double uneven = shortest + (even > nb ? even : nb);
         return uneven < rounds ? uneven : rounds;
     };
-    const bool hilo = p.rotate || p.k_axis != KVQ_PER_TOKEN || p.k_group == 32;
-    return (hilo ? 0.8 : 0.7) * estimate(kRows / 2) < estimate(kRows);
+    return 0.7 * estimate(kRows / 2) < estimate(kRows);
 }
 
 template <int D, int KG, bool W8, bool ROT>
