@@ -849,9 +849,12 @@ __device__ __forceinline__ void wait_vm(int n)
 }
 
 // The copies of this wave that precede the newest `after` of its issued
-// copies have landed, then every wave is past the same point.
+// copies have landed, then every wave is past the same point.  Products of the
+// stage that is given back must not sink below: a fragment they wait for could
+// still be on its way from LDS when another wave's copy overwrites it.
 __device__ __forceinline__ void ring_sync(int after)
 {
+    __builtin_amdgcn_sched_barrier(0);
     wait_vm(after);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");

@@ -1,4 +1,4 @@
-"""Wait states that inline assembly has to write out itself.
+"""Waits that the kernel sources have to write out themselves.
 
 On gfx9 a load into LDS that reads M0 must not directly follow a scalar write
 of M0: one wait state (an s_nop, or any other instruction) belongs between.
@@ -41,3 +41,18 @@ def test_no_lds_load_directly_after_an_m0_write():
             copies += any("load_lds" in i for i in instructions)
             assert not m0_hazards(instructions), f"{os.path.basename(path)}: {instructions}"
     assert copies >= 2  # the copies of the projection and the prefill kernels
+
+
+def test_bare_barriers_hold_back_earlier_products():
+    # __builtin_amdgcn_s_barrier alone lets the compiler sink register-only
+    # products, and the wait for the LDS reads that feed them, below the barrier,
+    # after which another wave's copy may overwrite what they read
+    bare = 0
+    for path in sorted(glob.glob(os.path.join(CSRC, "*"))):
+        with open(path) as f:
+            lines = f.read().splitlines()
+        for i, line in enumerate(lines):
+            if "__builtin_amdgcn_s_barrier()" in line:
+                bare += 1
+                assert any("__builtin_amdgcn_sched_barrier(0)" in x for x in lines[max(0, i - 3):i]), f"{path}:{i + 1}"
+    assert bare >= 4
